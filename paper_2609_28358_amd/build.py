@@ -18,7 +18,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmxconv.so")
 SOURCES = ["quantize.hip", "nvfp.hip", "im2col.hip", "conv_gemm.hip", "conv_lean.hip", "conv_lean_bwd.hip",
            "conv_lean_e4m3_fwd.hip", "conv_lean_e4m3_dg.hip", "conv_lean_e2m1_fwd.hip", "conv_lean_e2m1_dg.hip",
-           "conv_lean_nv.hip", "conv_lean_nv68.hip", "conv_lean_fp6.hip", "wgrad_lean.hip", "naive.hip", "netops.hip", "mxconv_abi.cpp"]
+           "conv_lean_nv.hip", "conv_lean_nv68.hip", "conv_lean_fp6.hip", "wgrad_lean.hip", "wgrad_row.hip", "naive.hip", "netops.hip", "mxconv_abi.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

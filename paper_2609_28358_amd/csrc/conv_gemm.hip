@@ -1396,9 +1396,16 @@ int launch_dgrad(const Conv& cv, const void* wc, const uint8_t* ws, const void* 
     return launch_conv(cv, true, wc, ws, gc, gs, gx, layout, s);
 }
 
+// Splits of a layer on the batch-block-32 kernels (0: the general kernels):
+// the kernel-row one's where it serves the layer, else the lean one's.
+static int bn32_splits(const Conv& cv) {
+    const int ls = wgrad_lean_splits(cv), rs = ls > 0 ? wgrad_row_splits(cv) : 0;
+    return rs > 0 ? rs : ls;
+}
+
 size_t wgrad_workspace(const Conv& cv) {
-    const int ls = wgrad_lean_splits(cv);
-    if (ls > 0) return ls > 1 ? (size_t)ls * cv.gy.cp * cv.kh * cv.kw * cv.x.cp * sizeof(float) : 0;
+    const int sp = bn32_splits(cv);
+    if (sp > 0) return sp > 1 ? (size_t)sp * cv.gy.cp * cv.kh * cv.kw * cv.x.cp * sizeof(float) : 0;
     if (!general_fmt(cv)) return 0;
     const WgradPlan pl = wgrad_plan(cv);
     return (size_t)pl.splits * cv.gy.cp * pl.ntot * sizeof(float);
@@ -1406,12 +1413,17 @@ size_t wgrad_workspace(const Conv& cv) {
 
 int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc, const uint8_t* xs,
                  float* gw, void* ws, hipStream_t s, const float* nv_tg, const float* nv_tx, bool defer) {
-    const int ls = wgrad_lean_splits(cv);
-    if (nv_tg && ls == 0) return MXC_ERR_SHAPE;
-    if (ls > 0) {
-        const int rc = launch_wgrad_lean(cv, gc, gs, xc, xs, ls > 1 ? (float*)ws : gw, ls, s, nv_tg, nv_tx);
-        if (rc || ls == 1 || defer) return rc;
-        return launch_reduce(cv, (const float*)ws, gw, ls, s);
+    int sp = bn32_splits(cv);
+    if (nv_tg && sp == 0) return MXC_ERR_SHAPE;
+    if (sp > 0) {
+        // NVFP operands run the lean kernel, within the workspace of the layer's MX form
+        if (nv_tg) sp = std::min(sp, wgrad_lean_splits(cv));
+        float* const dst = sp > 1 ? (float*)ws : gw;
+        const int rc = !nv_tg && wgrad_row_splits(cv) > 0
+                           ? launch_wgrad_row(cv, gc, gs, xc, xs, dst, s)
+                           : launch_wgrad_lean(cv, gc, gs, xc, xs, dst, sp, s, nv_tg, nv_tx);
+        if (rc || sp == 1 || defer) return rc;
+        return launch_reduce(cv, (const float*)ws, gw, sp, s);
     }
     if (!general_fmt(cv)) return MXC_ERR_SHAPE;
     const WgradPlan pl = wgrad_plan(cv);
@@ -1442,12 +1454,12 @@ int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* 
 int launch_backward(const Conv& dcv, const void* wc, const uint8_t* ws, const void* gc, const uint8_t* gs,
                     float* gx, int layout, const Conv& wcv, const void* xc, const uint8_t* xs, float* gw,
                     void* wsp, hipStream_t s, bool defer) {
-    const int ls = wgrad_lean_splits(wcv);
-    if (ls > 0) {
-        const int rc = launch_lean_bwd(dcv, wc, ws, gc, gs, gx, layout, wcv, xc, xs, ls > 1 ? (float*)wsp : gw, ls, s);
+    const int sp = bn32_splits(wcv);
+    if (sp > 0) {
+        const int rc = launch_lean_bwd(dcv, wc, ws, gc, gs, gx, layout, wcv, xc, xs, sp > 1 ? (float*)wsp : gw, sp, s);
         if (rc != 1) {
-            if (rc || ls == 1 || defer) return rc;
-            return launch_reduce(wcv, (const float*)wsp, gw, ls, s);
+            if (rc || sp == 1 || defer) return rc;
+            return launch_reduce(wcv, (const float*)wsp, gw, sp, s);
         }
     }
     const int rc = launch_dgrad(dcv, wc, ws, gc, gs, gx, layout, s);
@@ -1456,8 +1468,8 @@ int launch_backward(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
 }
 
 int wgrad_pending_splits(const Conv& cv) {
-    const int ls = wgrad_lean_splits(cv);
-    if (ls > 0) return ls > 1 ? ls : 0;
+    const int sp = bn32_splits(cv);
+    if (sp > 0) return sp > 1 ? sp : 0;
     return general_fmt(cv) ? wgrad_plan(cv).splits : 0;
 }
 

@@ -6,16 +6,24 @@ namespace mxc {
 
 namespace {
 
+struct WArgs {                // the weight gradient's arguments, by its tile
+    WLArgs l;
+    WRArgs r;
+};
+
 template <int F, int KW, int PW, bool DG2, int NB, int NRB = 2, bool KR = false>
-int bwd_launch(const LeanArgs& a, const WLArgs& q, int nl, int grid, size_t lds, hipStream_t s) {
+int bwd_launch(const LeanArgs& a, const WArgs& w, int nl, int grid, size_t lds, hipStream_t s) {
+    const BwdWArgs<KW, NB>* q;
+    if constexpr (KW == 3 && NB == 1) q = &w.r;
+    else                              q = &w.l;
     static std::atomic<uint64_t> devs{0};
     if (raise_lds(conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>, devs, lds)) return MXC_ERR_HIP;
-    hipLaunchKernelGGL((conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>), dim3(grid), dim3(LT), lds, s, a, q, nl);
+    hipLaunchKernelGGL((conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>), dim3(grid), dim3(LT), lds, s, a, *q, nl);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }
 
 template <int F, int NB>
-int bwd_launch_nb(const LeanArgs& a, const WLArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
+int bwd_launch_nb(const LeanArgs& a, const WArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
                   hipStream_t s) {
     if constexpr (F == MXC_E2M1) {
         if (pw == NARROW_PW) {
@@ -37,7 +45,7 @@ int bwd_launch_nb(const LeanArgs& a, const WLArgs& q, int nl, int grid, size_t l
 }
 
 template <int F>
-int bwd_launch_f(const LeanArgs& a, const WLArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
+int bwd_launch_f(const LeanArgs& a, const WArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
                  bool nb1, hipStream_t s) {
     return nb1 ? bwd_launch_nb<F, 1>(a, q, nl, grid, lds, dg2, kw, pw, kr, s)
                : bwd_launch_nb<F, 2>(a, q, nl, grid, lds, dg2, kw, pw, kr, s);
@@ -57,8 +65,14 @@ int launch_lean_bwd(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     const int prc = lean_plan(dcv, true, wc, ws, gc, gs, gx, layout, nullptr, nullptr, nullptr, P);
     if (prc) return prc;
     if (P.rb == 1 && P.pw != NARROW_PW) return 1;        // a narrow shape this kernel is not built for
-    WLArgs q;
-    const long wg = wgrad_lean_fill(wcv, gc, gs, xc, xs, wdst, splits, nullptr, nullptr, q);
+    WArgs q;
+    WRPlan wr;
+    const bool row = wgrad_row_plan(wcv, wr);
+    if (row && wr.nb != 1) return 1;                     // one wave per SIMD: a launch of its own
+    const bool nb1 = row || (wgrad_single_block(wcv) && wcv.kw == 1);
+    if (!row && !nb1 && wgrad_single_block(wcv)) return 1;
+    const long wg = row ? wgrad_row_fill(wcv, wr, gc, gs, xc, xs, wdst, q.r)
+                        : wgrad_lean_fill(wcv, gc, gs, xc, xs, wdst, splits, nullptr, nullptr, q.l);
     if (wg < 0) return MXC_ERR_SHAPE;
     LeanArgs& a = P.a;
     const long nl = ((long)(P.dg2 ? a.pofs[4] : a.ntiles) + 7) / 8 * 8;
@@ -66,7 +80,6 @@ int launch_lean_bwd(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     // ring depth for the combined grid, every workgroup holding at least the
     // LDS the weight-gradient tile sums its four waves through (64 KB, or
     // 16 KB on 32 x 32 tiles)
-    const bool nb1 = wgrad_single_block(wcv);
     const long red = nb1 ? 16384 : 65536;
     const long per_cu = (nl + wg + 255) / 256;
     int nbuf = 2;

@@ -40,11 +40,13 @@
 #pragma once
 
 #include <atomic>
+#include <type_traits>
 
 #include "mx_internal.h"
 
 namespace mxc {
 #include "wgrad_tile.h"
+#include "wgrad_row.h"
 
 struct LeanArgs {
     const uint8_t* wc;        // weight codes / scales
@@ -1084,8 +1086,11 @@ __global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void co
 // neither waits for the other, and the tail of one fills the CUs the other
 // leaves idle.  Both counts are multiples of 8, so each part keeps its own
 // kernel's XCD mapping.  Format F for every operand.
+// NB: the weight-gradient tile -- 2: 64 x 64 at one tap; 1: 32 x 32, of one
+// tap for 1-wide kernels, of a kernel row (wgrad_row.h) for 3-wide ones.
+template <int KW, int NB> using BwdWArgs = std::conditional_t<KW == 3 && NB == 1, WRArgs, WLArgs>;
 template <int F, int KW, int PW, bool DG2, int NB, int NRB = 2, bool KR = false>
-__global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void conv_lean_bwd_kernel(LeanArgs p, WLArgs q, int nl) {
+__global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void conv_lean_bwd_kernel(LeanArgs p, BwdWArgs<KW, NB> q, int nl) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int b = blockIdx.x;
     const int nw = (int)gridDim.x - nl;
@@ -1093,7 +1098,9 @@ __global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void co
         if constexpr (DG2) lean_dg2_body<F, F, KW, 1, PW, false, NRB, KR, false>(p, b - nw, nl);
         else               lean_body<F, F, true, KW, 1, 1, PW, false, NRB, KR, false>(p, b - nw, nl);
     } else {
-        wgrad_tile<F, F, false, NB, (NB == 1 && KW == 3) ? 3 : 1>(q, b, nw, (float (*)[32 * NB * 32 * NB])smem);
+        float (*const red)[32 * NB * 32 * NB] = (float (*)[32 * NB * 32 * NB])smem;
+        if constexpr (KW == 3 && NB == 1) wgrad_row_tile<F, F, 1, DG2 ? 2 : 1, 4>(q, b, nw, red);
+        else                              wgrad_tile<F, F, false, NB>(q, b, nw, red);
     }
 }
 

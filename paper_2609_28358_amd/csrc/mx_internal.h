@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <algorithm>
 #include "../../include/mxconv.h"
 
 namespace mxc {
@@ -130,12 +131,20 @@ int wgrad_lean_splits(const Conv& cv);
 inline bool wgrad_single_block(const Conv& cv) {
     return cv.gy.ncb == 1 && cv.x.ncb == 1 && cv.fa == cv.fb && (cv.fa == MXC_E4M3 || cv.fa == MXC_E2M1);
 }
-// taps of one kernel row a weight-gradient wave takes together: the three of
-// a 3-wide kernel on 32 x 32 MX tiles (G_Y loaded once for all three), else 1
-inline int wgrad_taps(const Conv& cv, bool nv) { return !nv && wgrad_single_block(cv) && cv.kw == 3 ? 3 : 1; }
 int launch_wgrad_lean(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc, const uint8_t* xs,
                       float* dst, int splits, hipStream_t s, const float* nv_tg = nullptr,
                       const float* nv_tx = nullptr);
+// the kernel-row weight gradient of 3-wide MX layers (wgrad_row.hip): the
+// tile side in 32-row blocks, tiles, row pairs and splits (false: another
+// kernel serves the layer); its splits, or 0; and the launch (dst: partial
+// tiles with more than one split, else G_W)
+struct WRPlan {
+    int nb, ntiles, nrp, splits;
+};
+bool wgrad_row_plan(const Conv& cv, WRPlan& q);
+int wgrad_row_splits(const Conv& cv);
+int launch_wgrad_row(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc, const uint8_t* xs, float* dst,
+                     hipStream_t s);
 size_t wgrad_workspace(const Conv& cv);
 int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc,
                  const uint8_t* xs, float* gw, void* ws, hipStream_t s, const float* nv_tg = nullptr,

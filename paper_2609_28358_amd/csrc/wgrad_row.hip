@@ -1,0 +1,100 @@
+// wgrad_row.hip -- a5 for 3-wide kernels with batch block 32: the kernel-row
+// weight-gradient tile (wgrad_row.h), its launch planning and dispatch.
+#include "mx_internal.h"
+
+namespace mxc {
+
+#include "wgrad_row.h"
+
+namespace {
+
+// Operand slots in flight (steps): as many as the registers beside the
+// accumulators hold without spilling; deeper rings measured no faster.
+template <int FA, int FB, int NB>
+constexpr int wr_depth() { return NB == 2 && (FA == MXC_E4M3 || fmt_bits(FB) == 6) ? 3 : 4; }
+
+template <int FA, int FB, int NB, int S>
+__global__ __launch_bounds__(WRT, NB == 2 ? 1 : 2) void wgrad_row_kernel(WRArgs p) {
+    __shared__ float red[4][32 * NB * 32 * NB];
+    wgrad_row_tile<FA, FB, NB, S, wr_depth<FA, FB, NB>()>(p, blockIdx.x, gridDim.x, red);
+}
+
+template <int FA, int FB>
+void wr_launch(const WRArgs& a, int nb, int sw, dim3 gd, hipStream_t s) {
+    if (nb == 2) {
+        // FP4 / FP6 take 64 x 64 tiles at column stride 1 only
+        if (FA != MXC_E4M3 || sw == 1) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 1>), gd, dim3(WRT), 0, s, a);
+        else if constexpr (FA == MXC_E4M3)
+            hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 2>), gd, dim3(WRT), 0, s, a);
+    }
+    else if (sw == 2) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 2>), gd, dim3(WRT), 0, s, a);
+    else              hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 1>), gd, dim3(WRT), 0, s, a);
+}
+
+}  // namespace
+
+// Tile shape and splits of the kernel-row weight gradient; false when the
+// layer is outside it or better off with the 64 x 64 tile of one tap
+// (wgrad_tile.h).  Measured for the whole gradient, reduction included:
+//   one channel block on each side: always (stem at batch 32 59 -> 37 us,
+//     16 -> 16 channels at 160 x 160, batch 64, 37 -> 22 us);
+//   FP8: always, the decoded window saves two of three decodes; 64 x 64 tiles
+//     where a wave walks at least 12 columns (256 -> 256 at 16 x 16, batch 128,
+//     89 -> 53 us), else 32 x 32 ones (64 -> 64 at 56 x 56, batch 32, 27 -> 19);
+//   FP4 / FP6 on more blocks: 64 x 64 tiles where a wave walks enough columns
+//     to cover the larger epilogue, column stride 1 (256 -> 256 as above 40 ->
+//     34; FP6 128 -> 128 at 40 x 40, batch 64, 33 -> 29); FP4 needs more of
+//     them, since its one-tap tiles share a launch with the input gradient
+//     (128 -> 128 at 40 x 40: 29 -> 27 alone, but 44 -> 47 us with it);
+//     32 x 32 tiles where there are few columns in all (128 -> 256, stride 2,
+//     at 28 x 28, batch 32: 17 -> 14), a one-tap tile's wave having hardly
+//     any to walk.
+bool wgrad_row_plan(const Conv& cv, WRPlan& q) {
+    if (cv.x.bn != 32 || cv.kw != 3 || (cv.sw != 1 && cv.sw != 2)) return false;
+    const long gb = (long)cv.gy.ng * cv.ho * cv.wo * cv.gy.cp * 4 * fmt_bits(cv.fa);
+    const long xb = (long)cv.x.ng * cv.h * cv.w * cv.x.cp * 4 * fmt_bits(cv.fb);
+    if (gb >= 0x7FFFFF00L || xb >= 0x7FFFFF00L) return false;   // 32-bit buffer offsets
+    q.nrp = (cv.x.ng * cv.ho + 1) / 2;
+    const long total = (long)q.nrp * cv.wo;                           // columns of all row pairs
+    const long part = (long)cv.gy.cp * cv.kh * 3 * cv.x.cp * 4;       // bytes of one partial result
+    auto tiles = [&](int n) { return (long)cv.kh * ((cv.gy.ncb + n - 1) / n) * ((cv.x.ncb + n - 1) / n); };
+    // one workgroup per CU on 64 x 64 tiles (a wave per SIMD by their
+    // registers), two on 32 x 32 ones; a wave walks at least 6 columns; the
+    // partial results stay within 16 MiB
+    auto split = [&](int n) {
+        return std::max(1L, std::min({(n == 2 ? 256 : 512) / tiles(n), total / (4 * 6), (16L << 20) / part}));
+    };
+    q.nb = 1;
+    if (cv.gy.ncb > 1 || cv.x.ncb > 1) {
+        const long cols = cv.gy.ncb > 1 && cv.x.ncb > 1 ? total / (4 * split(2)) : 0;
+        if (cv.fa == MXC_E4M3) q.nb = cols >= 12 ? 2 : 1;
+        else if (cv.sw == 1 && cols >= (fmt_bits(cv.fb) == 6 ? 16 : 24)) q.nb = 2;
+        else if (total > 128) return false;
+    }
+    const long nt = tiles(q.nb);
+    if (nt > 0x7FFFFFL) return false;
+    q.ntiles = (int)nt;
+    q.splits = (int)split(q.nb);
+    return true;
+}
+
+int wgrad_row_splits(const Conv& cv) {
+    WRPlan q;
+    return wgrad_row_plan(cv, q) ? q.splits : 0;
+}
+
+int launch_wgrad_row(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc, const uint8_t* xs, float* dst,
+                     hipStream_t s) {
+    WRPlan q;
+    if (!wgrad_row_plan(cv, q)) return MXC_ERR_SHAPE;
+    WRArgs a;
+    const dim3 gd((unsigned)wgrad_row_fill(cv, q, gc, gs, xc, xs, dst, a));
+    if (cv.fa == MXC_E4M3 && cv.fb == MXC_E4M3)      wr_launch<MXC_E4M3, MXC_E4M3>(a, q.nb, cv.sw, gd, s);
+    else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E2M1) wr_launch<MXC_E2M1, MXC_E2M1>(a, q.nb, cv.sw, gd, s);
+    else if (cv.fa == MXC_E2M3 && cv.fb == MXC_E2M3) wr_launch<MXC_E2M3, MXC_E2M3>(a, q.nb, cv.sw, gd, s);
+    else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E3M2) wr_launch<MXC_E2M1, MXC_E3M2>(a, q.nb, cv.sw, gd, s);
+    else return MXC_ERR_ARG;
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
+}
+
+}  // namespace mxc

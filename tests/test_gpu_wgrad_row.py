@@ -1,0 +1,93 @@
+"""The kernel-row weight gradient (3-wide kernels, batch block 32) at the edges
+of its tiles: one column, an odd number of output rows, rows and columns of
+padding wider than the input, unequal row and column strides, kernels of one
+and five rows, channels that fill no block, tiles of 32 x 32 and 64 x 64, one
+split and many -- against the oracle, within 1e-5 of the sum of absolute
+products, and mxconv_backward equal to it bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import mx_tolerance as mxt
+import oracle
+from paper_2609_28358_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+SAMPLES = 3000
+
+
+@pytest.fixture(scope="module")
+def mx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_28358_amd import mxconv
+    mxconv.lib()
+    return mxconv
+
+
+def _cv(n, cin, cout, h, w, kh=3, sh=1, sw=1, ph=1, pw=1):
+    return dict(n=n, cin=cin, cout=cout, h=h, w=w, kh=kh, kw=3, sh=sh, sw=sw, ph=ph, pw=pw)
+
+
+LAYERS = [
+    _cv(32, 3, 16, 31, 33, sw=2, sh=2),              # the stem's shape, odd sizes
+    _cv(32, 32, 32, 1, 1),                           # one pixel: every tap but the middle in the padding
+    _cv(96, 24, 20, 5, 1),                           # one column, an odd number of rows over three groups
+    _cv(32, 16, 32, 3, 4, pw=2, ph=2),               # padding on both sides of every row
+    _cv(64, 40, 24, 9, 7, kh=1, ph=0),               # one kernel row, two channel blocks against one
+    _cv(32, 33, 65, 12, 11, kh=5, sh=2, sw=1, ph=2),
+    _cv(32, 32, 64, 10, 13, sh=1, sw=2, pw=0),
+    _cv(32, 8, 8, 40, 57),                           # many splits, some waves past the end
+    _cv(64, 70, 72, 33, 63),                         # 64 x 64 tiles, the third block of each side alone
+    _cv(64, 70, 72, 65, 64, sh=2, sw=2),
+]
+
+
+def _operands(mx, cv, fg, fx, seed, x=None, gy=None):
+    if x is None:
+        x, _, gy = synth.layer_inputs(cv, seed, kind="sweep")
+    q = [mx.quantize(synth.nchw_to_cbf(t, 32).to(DEV), mx.ACT, f, layout=mx.CBF, shape=tuple(t.shape))
+         for t, f in ((gy, fg), (x, fx))]
+    o = [oracle.quantize(t.numpy(), oracle.NCHW, oracle.ACT, f, *t.shape) for t, f in ((gy, fg), (x, fx))]
+    return q, o
+
+
+@pytest.mark.parametrize("fg,fx", [(0, 0), (1, 1), (2, 2), (1, 3)])
+@pytest.mark.parametrize("k", range(len(LAYERS)))
+def test_against_oracle(mx, k, fg, fx):
+    cv = LAYERS[k]
+    (qg, qx), (og, ox) = _operands(mx, cv, fg, fx, 900 + k)
+    gw = torch.full((cv["cout"], cv["cin"], cv["kh"], 3), 9.0, device=DEV)
+    ws = torch.full((max(16, mx.wgrad_workspace_bytes(cv, mx.pair(fg, fx))),), 255, dtype=torch.uint8, device=DEV)
+    mx.wgrad(cv, qg, qx, out=gw, workspace=ws)
+    dims = tuple(gw.shape)
+    rng = np.random.default_rng(k)
+    idx = (np.stack(np.meshgrid(*[np.arange(d) for d in dims], indexing="ij"), -1).reshape(-1, 4)
+           if np.prod(dims) <= SAMPLES else np.stack([rng.integers(0, d, SAMPLES) for d in dims], 1))
+    r, s = oracle.wgrad_at(cv, fg if fg == fx else (fg, fx), og, ox, idx)
+    got = gw.cpu().numpy()[tuple(idx.T)]
+    err = mxt.gemm_err(got, r, s)
+    assert err <= 1.0, f"layer {k}: error is {err:.3f} of the allowed bound"
+    if fg == fx:
+        w = synth.kaiming(cv["cout"], cv["cin"], cv["kh"], 3, 1)
+        qw = mx.quantize(w.to(DEV), mx.WEIGHT, fg)
+        if cv["sh"] == cv["sw"] or fg < 2:
+            gw2 = mx.backward(cv, qw, qg, qx)[1]
+            torch.cuda.synchronize()
+            assert torch.equal(gw, gw2), f"layer {k}: backward's weight gradient differs"
+
+
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("cv", [_cv(32, 24, 24, 6, 5), _cv(64, 70, 72, 33, 63)], ids=["32x32", "64x64"])
+def test_a_nan_reaches_its_taps_only(mx, fmt, cv):
+    """A non-finite X pixel in the first column meets the taps whose window
+    covers it, not the ones that would reach it from outside the output."""
+    x, _, gy = synth.layer_inputs(cv, 77, kind="sweep")
+    x[0, 1, :, 0] = float("nan")                     # column 0, every row: taps 0 and 1 of each kernel row
+    (qg, qx), _ = _operands(mx, cv, fmt, fmt, 0, x, gy)
+    gw = mx.wgrad(cv, qg, qx).cpu()
+    assert torch.isnan(gw[:, :32, :, :2]).all()      # the whole 32-channel block shares the NaN scale
+    assert not torch.isnan(gw[:, :, :, 2]).any()
+    assert not torch.isnan(gw[:, 32:]).any()
