@@ -78,74 +78,111 @@ struct SumArgs {
     int fn;
     const void* z;                    // CBF [n/32][h][w][c][32] (fn != NONE), fp32 or bf16 (BF)
     float* vals;                      // optional: the values quantized
-    int sr;                           // codes by stochastic rounding, generator key (k0, k1)
-    uint32_t k0, k1;
+    uint32_t k0, k1;                  // stochastic rounding (SR): generator key
 };
 
-// Four consecutive elements at index i of an fp32 or (BF) bf16 tensor.
-template <bool BF>
-__device__ __forceinline__ float4 load4(const void* s, size_t i) {
-    if constexpr (BF) return bf16_unpack4(load_nt((const unsigned short*)s + i));
-    else              return load_nt((const float*)s + i);
-}
-
 // Term t at destination pixel (g, y, x), channel ch, samples j .. j+3.
-template <bool BF>
 __device__ __forceinline__ float4 term4(const SumArgs& a, int t, long long g, int y, int x, int ch, int j) {
-    const void* s = a.src[t];
+    const float* s = (const float*)a.src[t];
     const int cs = a.c_src[t];
     const int col = a.c_off[t] + ch;
-    if (!a.down[t]) {
-        const size_t i = ((((size_t)g * a.h + y) * a.w + x) * cs + col) * 32 + j;
-        return load4<BF>(s, i);
-    }
+    if (!a.down[t]) return load_nt(s + ((((size_t)g * a.h + y) * a.w + x) * cs + col) * 32 + j);
     const int hs = 2 * a.h, ws = 2 * a.w;
     const size_t r0 = ((size_t)g * hs + 2 * y) * ws + 2 * x, r1 = r0 + ws;
-    const float4 p = load4<BF>(s, (r0 * cs + col) * 32 + j);
-    const float4 q = load4<BF>(s, ((r0 + 1) * cs + col) * 32 + j);
-    const float4 u = load4<BF>(s, (r1 * cs + col) * 32 + j);
-    const float4 v = load4<BF>(s, ((r1 + 1) * cs + col) * 32 + j);
+    const float4 p = load_nt(s + (r0 * cs + col) * 32 + j);
+    const float4 q = load_nt(s + ((r0 + 1) * cs + col) * 32 + j);
+    const float4 u = load_nt(s + (r1 * cs + col) * 32 + j);
+    const float4 v = load_nt(s + ((r1 + 1) * cs + col) * 32 + j);
     return make_float4((p.x + q.x) + (u.x + v.x), (p.y + q.y) + (u.y + v.y), (p.z + q.z) + (u.z + v.z),
                        (p.w + q.w) + (u.w + v.w));
 }
 
-template <int FMT, bool BF>
+// The block of this wave, in scalar registers (a wave-uniform index that the
+// compiler cannot see as one makes every address and division of it vector
+// work: the 64-bit divisions alone were about as many instructions as the
+// block's values), and the pixel and channel block it is.
+__device__ __forceinline__ uint32_t wave_block() {
+    return blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// NT: 1 or 2 terms none of which is a 2x2 patch sum, all loads issued before
+// the first value is used; 0: any terms.  Bound by HBM: measured with one
+// term and SiLU', 32 channels at 160 x 160, batch 64, bf16 60.8 -> 47.6 us
+// (236 MB: the copy rate), 16 channels 38.5 -> 26.2; fp32, 256 channels at
+// 16 x 16, batch 128, 15.4 -> 12.2 us.
+template <int FMT, int NT, bool SR>
 __global__ __launch_bounds__(256) void quantize_sum_kernel(SumArgs a, uint8_t* __restrict__ codes,
-                                                           uint8_t* __restrict__ scales, long long nblocks) {
-    const long long blk = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                           uint8_t* __restrict__ scales, uint32_t nblocks) {
+    const uint32_t blk = wave_block();
     if (blk >= nblocks) return;
     const int lane = threadIdx.x & 63;
-    const int cb = (int)(blk % a.ncb);
-    const long long pix = blk / a.ncb;                     // (group, y, x)
-    const int x = (int)(pix % a.w);
-    const long long gy = pix / a.w;
-    const int y = (int)(gy % a.h);
-    const long long g = gy / a.h;
+    const uint32_t pix = blk / (uint32_t)a.ncb;            // (group, y, x)
+    const int cb = (int)(blk - pix * (uint32_t)a.ncb);
     const int j = 4 * (lane & 7);
     float4 v[4];
+    if constexpr (NT > 0) {
+        float4 u[NT][4], zz[4];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int ch = cb * 32 + 8 * q + (lane >> 3);
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ch < a.c) {
-            s = term4<BF>(a, 0, g, y, x, ch, j);
-            for (int t = 1; t < a.nterms; t++) {
-                const float4 u = term4<BF>(a, t, g, y, x, ch, j);
-                s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
-            }
-            if (a.fn != MXC_FN_NONE) {
-                const float4 zz = load4<BF>(a.z, ((size_t)pix * a.c + ch) * 32 + j);
-                with_fn(a.fn, [&](auto t) {
-                    constexpr int F = decltype(t)::fn;
-                    s.x *= fn_grad_c<F>(zz.x);
-                    s.y *= fn_grad_c<F>(zz.y);
-                    s.z *= fn_grad_c<F>(zz.z);
-                    s.w *= fn_grad_c<F>(zz.w);
-                });
-            }
-            if (a.vals) store_nt(a.vals + ((size_t)pix * a.c + ch) * 32 + j, s);
+        for (int q = 0; q < 4; q++) {
+            const int ch = cb * 32 + 8 * q + (lane >> 3);
+            const bool ok = ch < a.c;
+#pragma unroll
+            for (int t = 0; t < NT; t++)
+                u[t][q] = ok ? load_nt((const float*)a.src[t] + ((size_t)pix * a.c_src[t] + a.c_off[t] + ch) * 32 + j)
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+            zz[q] = ok && a.fn != MXC_FN_NONE ? load_nt((const float*)a.z + ((size_t)pix * a.c + ch) * 32 + j)
+                                              : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        v[q] = s;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            v[q] = u[0][q];
+            if constexpr (NT == 2) { v[q].x += u[1][q].x; v[q].y += u[1][q].y; v[q].z += u[1][q].z; v[q].w += u[1][q].w; }
+        }
+        if (a.fn != MXC_FN_NONE)
+            with_fn(a.fn, [&](auto t) {
+                constexpr int F = decltype(t)::fn;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    v[q].x *= fn_grad_c<F>(zz[q].x);
+                    v[q].y *= fn_grad_c<F>(zz[q].y);
+                    v[q].z *= fn_grad_c<F>(zz[q].z);
+                    v[q].w *= fn_grad_c<F>(zz[q].w);
+                }
+            });
+#pragma unroll
+        for (int q = 0; q < 4; q++) {                      // (padding rows: 0 times fn'(0) >= 0)
+            const int ch = cb * 32 + 8 * q + (lane >> 3);
+            if (ch < a.c && a.vals) store_nt(a.vals + ((size_t)pix * a.c + ch) * 32 + j, v[q]);
+        }
+    } else {
+        const int x = (int)(pix % (uint32_t)a.w);
+        const uint32_t gy = pix / (uint32_t)a.w;
+        const int y = (int)(gy % (uint32_t)a.h);
+        const long long g = gy / (uint32_t)a.h;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int ch = cb * 32 + 8 * q + (lane >> 3);
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ch < a.c) {
+                s = term4(a, 0, g, y, x, ch, j);
+                for (int t = 1; t < a.nterms; t++) {
+                    const float4 u = term4(a, t, g, y, x, ch, j);
+                    s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+                }
+                if (a.fn != MXC_FN_NONE) {
+                    const float4 zz = load_nt((const float*)a.z + ((size_t)pix * a.c + ch) * 32 + j);
+                    with_fn(a.fn, [&](auto t) {
+                        constexpr int F = decltype(t)::fn;
+                        s.x *= fn_grad_c<F>(zz.x);
+                        s.y *= fn_grad_c<F>(zz.y);
+                        s.z *= fn_grad_c<F>(zz.z);
+                        s.w *= fn_grad_c<F>(zz.w);
+                    });
+                }
+                if (a.vals) store_nt(a.vals + ((size_t)pix * a.c + ch) * 32 + j, s);
+            }
+            v[q] = s;
+        }
     }
     uint32_t m = 0;
 #pragma unroll
@@ -161,7 +198,7 @@ __global__ __launch_bounds__(256) void quantize_sum_kernel(SumArgs a, uint8_t* _
     const float inv = inv_scale(sc);
     const bool bad = sc == 0xFFu;
     uint32_t run[4];   // the codes of v[q]: channel row 8 q + lane / 8, samples j .. j + 3
-    if (a.sr) {        // stochastic rounding, keyed by code position blk 1024 + 32 row + sample
+    if constexpr (SR) {   // stochastic rounding, keyed by code position blk 1024 + 32 row + sample
         const int s = (int)sc - 127;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
@@ -200,63 +237,109 @@ __device__ __forceinline__ uint4 load16_nt(const uint16_t* p) {   // 16 bytes, b
     return make_uint4(__float_as_uint(f.x), __float_as_uint(f.y), __float_as_uint(f.z), __float_as_uint(f.w));
 }
 
-template <int FMT>
+template <int FMT, int NT, bool SR>
 __global__ __launch_bounds__(256) void quantize_sum_bf_kernel(SumArgs a, uint8_t* __restrict__ codes,
-                                                              uint8_t* __restrict__ scales, long long nblocks) {
-    const long long blk = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                              uint8_t* __restrict__ scales, uint32_t nblocks) {
+    const uint32_t blk = wave_block();
     if (blk >= nblocks) return;
     const int lane = threadIdx.x & 63;
-    const int cb = (int)(blk % a.ncb);
-    const long long pix = blk / a.ncb;                     // (group, y, x)
-    const int x = (int)(pix % a.w);
-    const long long gy = pix / a.w;
-    const int y = (int)(gy % a.h);
-    const long long g = gy / a.h;
+    const uint32_t pix = blk / (uint32_t)a.ncb;            // (group, y, x)
+    const int cb = (int)(blk - pix * (uint32_t)a.ncb);
     const int j = 8 * (lane & 3);
-    const int hs = 2 * a.h, ws = 2 * a.w;
-    const size_t r0 = ((size_t)g * hs + 2 * y) * ws + 2 * x, r1 = r0 + ws;   // a 2x2 source patch (down)
     float v[2][8];
+    if constexpr (NT > 0) {
+        const bool two = cb * 32 + 16 < a.c;               // the block's second sixteen rows hold channels
+        uint4 u[2][NT], zz[2];
 #pragma unroll
-    for (int hh = 0; hh < 2; hh++) {
-        const int ch = cb * 32 + 16 * hh + (lane >> 2);
+        for (int hh = 0; hh < 2; hh++) {
+            const int ch = cb * 32 + 16 * hh + (lane >> 2);
+            const bool ok = ch < a.c;
+            zz[hh] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-        for (int e = 0; e < 8; e++) v[hh][e] = 0.0f;
-        if (ch >= a.c) continue;
-        for (int t = 0; t < a.nterms; t++) {
-            const uint16_t* src = (const uint16_t*)a.src[t];
-            const int cs = a.c_src[t], col = a.c_off[t] + ch;
-            float u[8];
-            if (!a.down[t]) {
-                bf16x8(load16_nt(src + ((size_t)pix * cs + col) * 32 + j), u);
-            } else {
-                float p0[8], p1[8], p2[8], p3[8];
-                bf16x8(load16_nt(src + (r0 * cs + col) * 32 + j), p0);
-                bf16x8(load16_nt(src + ((r0 + 1) * cs + col) * 32 + j), p1);
-                bf16x8(load16_nt(src + (r1 * cs + col) * 32 + j), p2);
-                bf16x8(load16_nt(src + ((r1 + 1) * cs + col) * 32 + j), p3);
+            for (int t = 0; t < NT; t++) u[hh][t] = zz[hh];
+            if (hh == 1 && !two) continue;                 // wave-uniform
 #pragma unroll
-                for (int e = 0; e < 8; e++) u[e] = (p0[e] + p1[e]) + (p2[e] + p3[e]);
+            for (int t = 0; t < NT; t++)
+                if (ok)
+                    u[hh][t] = load16_nt((const uint16_t*)a.src[t] +
+                                         ((size_t)pix * a.c_src[t] + a.c_off[t] + ch) * 32 + j);
+            if (ok && a.fn != MXC_FN_NONE) zz[hh] = load16_nt((const uint16_t*)a.z + ((size_t)pix * a.c + ch) * 32 + j);
+        }
+#pragma unroll
+        for (int hh = 0; hh < 2; hh++) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[hh][e] = 0.0f;
+            if (hh == 1 && !two) continue;
+            const int ch = cb * 32 + 16 * hh + (lane >> 2);
+            float w[8];
+            bf16x8(u[hh][0], v[hh]);
+            if constexpr (NT == 2) {
+                bf16x8(u[hh][1], w);
+#pragma unroll
+                for (int e = 0; e < 8; e++) v[hh][e] += w[e];
             }
-            if (t == 0) {
+            if (a.fn != MXC_FN_NONE) {
+                bf16x8(zz[hh], w);
+                with_fn(a.fn, [&](auto t) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) v[hh][e] = u[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; e++) v[hh][e] += u[e];
+                    for (int e = 0; e < 8; e++) v[hh][e] *= fn_grad_c<decltype(t)::fn>(w[e]);
+                });
+            }
+            if (a.vals && ch < a.c) {
+                float* o = a.vals + ((size_t)pix * a.c + ch) * 32 + j;
+                store_nt(o, make_float4(v[hh][0], v[hh][1], v[hh][2], v[hh][3]));
+                store_nt(o + 4, make_float4(v[hh][4], v[hh][5], v[hh][6], v[hh][7]));
             }
         }
-        if (a.fn != MXC_FN_NONE) {
-            float z[8];
-            bf16x8(load16_nt((const uint16_t*)a.z + ((size_t)pix * a.c + ch) * 32 + j), z);
-            with_fn(a.fn, [&](auto t) {
+    } else {
+        const int x = (int)(pix % (uint32_t)a.w);
+        const uint32_t gy = pix / (uint32_t)a.w;
+        const int y = (int)(gy % (uint32_t)a.h);
+        const long long g = gy / (uint32_t)a.h;
+        const int hs = 2 * a.h, ws = 2 * a.w;
+        const size_t r0 = ((size_t)g * hs + 2 * y) * ws + 2 * x, r1 = r0 + ws;   // a 2x2 source patch (down)
 #pragma unroll
-                for (int e = 0; e < 8; e++) v[hh][e] *= fn_grad_c<decltype(t)::fn>(z[e]);
-            });
-        }
-        if (a.vals) {
-            float* o = a.vals + ((size_t)pix * a.c + ch) * 32 + j;
-            store_nt(o, make_float4(v[hh][0], v[hh][1], v[hh][2], v[hh][3]));
-            store_nt(o + 4, make_float4(v[hh][4], v[hh][5], v[hh][6], v[hh][7]));
+        for (int hh = 0; hh < 2; hh++) {
+            const int ch = cb * 32 + 16 * hh + (lane >> 2);
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[hh][e] = 0.0f;
+            if (ch >= a.c) continue;
+            for (int t = 0; t < a.nterms; t++) {
+                const uint16_t* src = (const uint16_t*)a.src[t];
+                const int cs = a.c_src[t], col = a.c_off[t] + ch;
+                float u[8];
+                if (!a.down[t]) {
+                    bf16x8(load16_nt(src + ((size_t)pix * cs + col) * 32 + j), u);
+                } else {
+                    float p0[8], p1[8], p2[8], p3[8];
+                    bf16x8(load16_nt(src + (r0 * cs + col) * 32 + j), p0);
+                    bf16x8(load16_nt(src + ((r0 + 1) * cs + col) * 32 + j), p1);
+                    bf16x8(load16_nt(src + (r1 * cs + col) * 32 + j), p2);
+                    bf16x8(load16_nt(src + ((r1 + 1) * cs + col) * 32 + j), p3);
+#pragma unroll
+                    for (int e = 0; e < 8; e++) u[e] = (p0[e] + p1[e]) + (p2[e] + p3[e]);
+                }
+                if (t == 0) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[hh][e] = u[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[hh][e] += u[e];
+                }
+            }
+            if (a.fn != MXC_FN_NONE) {
+                float z[8];
+                bf16x8(load16_nt((const uint16_t*)a.z + ((size_t)pix * a.c + ch) * 32 + j), z);
+                with_fn(a.fn, [&](auto t) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[hh][e] *= fn_grad_c<decltype(t)::fn>(z[e]);
+                });
+            }
+            if (a.vals) {
+                float* o = a.vals + ((size_t)pix * a.c + ch) * 32 + j;
+                store_nt(o, make_float4(v[hh][0], v[hh][1], v[hh][2], v[hh][3]));
+                store_nt(o + 4, make_float4(v[hh][4], v[hh][5], v[hh][6], v[hh][7]));
+            }
         }
     }
     uint32_t m = 0;
@@ -275,7 +358,7 @@ __global__ __launch_bounds__(256) void quantize_sum_bf_kernel(SumArgs a, uint8_t
         const float4 hi = make_float4(v[hh][4], v[hh][5], v[hh][6], v[hh][7]);
         const int row = 16 * hh + (lane >> 2);
         uint32_t clo, chi;   // the codes of lo and hi (samples j .. j + 3, j + 4 .. j + 7)
-        if (a.sr) {          // stochastic rounding: positions blk 1024 + 32 row + j .., one generator call
+        if constexpr (SR) {  // stochastic rounding: positions blk 1024 + 32 row + j .., one generator call
             const int s = (int)sc - 127;
             const uint4 w = sr_words(((uint64_t)blk * 1024 + row * 32 + j) >> 3, a.k0, a.k1);
             const uint32_t r[8] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16,
@@ -301,6 +384,20 @@ __global__ __launch_bounds__(256) void quantize_sum_bf_kernel(SumArgs a, uint8_t
             *(uint32_t*)(codes + (size_t)blk * 512 + row * 16 + j / 2) = c;
         }
     }
+}
+
+template <int FMT, int NT, bool SR>
+void launch_sum_nt(const SumArgs& a, bool bf16, dim3 gd, uint8_t* codes, uint8_t* scales, uint32_t nblocks,
+                   hipStream_t s) {
+    if (bf16) hipLaunchKernelGGL((quantize_sum_bf_kernel<FMT, NT, SR>), gd, dim3(256), 0, s, a, codes, scales, nblocks);
+    else      hipLaunchKernelGGL((quantize_sum_kernel<FMT, NT, SR>), gd, dim3(256), 0, s, a, codes, scales, nblocks);
+}
+template <int FMT, bool SR>
+void launch_sum(const SumArgs& a, int nt, bool bf16, dim3 gd, uint8_t* codes, uint8_t* scales, uint32_t nblocks,
+                hipStream_t s) {
+    if (nt == 1)      launch_sum_nt<FMT, 1, SR>(a, bf16, gd, codes, scales, nblocks, s);
+    else if (nt == 2) launch_sum_nt<FMT, 2, SR>(a, bf16, gd, codes, scales, nblocks, s);
+    else              launch_sum_nt<FMT, 0, SR>(a, bf16, gd, codes, scales, nblocks, s);
 }
 
 }  // namespace
@@ -334,7 +431,6 @@ int launch_quantize_sum(const Geom& dst, int fmt, const mxc_term* terms, int nte
                         const void* z, void* codes, uint8_t* scales, float* vals, hipStream_t s, bool sr,
                         uint64_t seed) {
     SumArgs a{};
-    a.sr = sr ? 1 : 0;
     a.k0 = (uint32_t)seed;
     a.k1 = (uint32_t)(seed >> 32);
     for (int t = 0; t < nterms; t++) {
@@ -350,17 +446,17 @@ int launch_quantize_sum(const Geom& dst, int fmt, const mxc_term* terms, int nte
     a.vals = vals;
     const long long nblocks = (long long)dst.ng * dst.h * dst.w * dst.ncb;
     if (nblocks <= 0) return MXC_OK;
-    const long long grid = (nblocks + 3) / 4;
-    if (grid > 0x7FFFFFFFLL) return MXC_ERR_SHAPE;
-    const dim3 gd((unsigned)grid);
+    if (nblocks > 0x7FFFFFFFLL) return MXC_ERR_SHAPE;
+    const dim3 gd((unsigned)((nblocks + 3) / 4));
+    bool plain = nterms <= 2;
+    for (int t = 0; t < nterms; t++) plain &= !terms[t].down;
+    const int nt = plain ? nterms : 0;
     uint8_t* const cd = (uint8_t*)codes;
-    if (fmt == MXC_E4M3) {
-        if (bf16) hipLaunchKernelGGL((quantize_sum_bf_kernel<MXC_E4M3>), gd, dim3(256), 0, s, a, cd, scales, nblocks);
-        else      hipLaunchKernelGGL((quantize_sum_kernel<MXC_E4M3, false>), gd, dim3(256), 0, s, a, cd, scales, nblocks);
-    } else {
-        if (bf16) hipLaunchKernelGGL((quantize_sum_bf_kernel<MXC_E2M1>), gd, dim3(256), 0, s, a, cd, scales, nblocks);
-        else      hipLaunchKernelGGL((quantize_sum_kernel<MXC_E2M1, false>), gd, dim3(256), 0, s, a, cd, scales, nblocks);
-    }
+    const uint32_t nb = (uint32_t)nblocks;
+    if (fmt == MXC_E4M3) sr ? launch_sum<MXC_E4M3, true>(a, nt, bf16, gd, cd, scales, nb, s)
+                            : launch_sum<MXC_E4M3, false>(a, nt, bf16, gd, cd, scales, nb, s);
+    else                 sr ? launch_sum<MXC_E2M1, true>(a, nt, bf16, gd, cd, scales, nb, s)
+                            : launch_sum<MXC_E2M1, false>(a, nt, bf16, gd, cd, scales, nb, s);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }
 

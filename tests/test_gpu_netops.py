@@ -136,3 +136,28 @@ def test_quantize_sum_errors(mx):
         mx.quantize_sum(ok, (32, 32, 4, 4), 2)                       # FP6 not offered
     with pytest.raises(mx.MxconvError, match="code -1"):
         mx.quantize_sum(ok, (32, 32, 4, 4), 0, fn=mx.FN_SILU)        # SiLU' needs z
+
+
+@pytest.mark.parametrize("sr", [None, 5], ids=["rne", "sr"])
+@pytest.mark.parametrize("bf", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
+@pytest.mark.parametrize("c,nt,fn", [(8, 1, 2), (16, 2, 2), (17, 1, 1), (48, 2, 0), (72, 1, 2)])
+def test_quantize_sum_few_terms_as_many(mx, c, nt, fn, fmt, bf, sr):
+    """One or two plain terms take a path of their own: the same codes, scales
+    and values as the path for any terms (three or more; the further ones zero)."""
+    dt = torch.bfloat16 if bf else torch.float32
+    cbf = lambda ch, std, seed: synth.nchw_to_cbf(synth.normal((64, ch, 5, 3), std, seed), 32).to(dt).to(DEV)
+    terms = [(cbf(c + 8 * k, 1e-3, 30 + k), c + 8 * k, 8 * k, 0) for k in range(nt)]
+    zero = [(torch.zeros_like(terms[0][0]), c, 0, 0)] * (3 - nt)
+    z = cbf(c, 2.0, 40)
+    got = []
+    for ts in (terms, terms + zero):
+        vals = torch.full((2, 5, 3, c, 32), float("nan"), device=DEV)
+        out = mx.MxTensor.empty(mx.ACT, fmt, (64, c, 5, 3), DEV)
+        _garbage(out.codes), _garbage(out.scales)
+        mx.quantize_sum(ts, (64, c, 5, 3), fmt, fn=fn | (mx.FN_BF16 if bf else 0), z=z if fn else None, out=out,
+                        vals=vals, sr_seed=sr)
+        got.append((out.codes, out.scales, vals))
+    torch.cuda.synchronize()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
