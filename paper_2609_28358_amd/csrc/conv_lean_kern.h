@@ -907,7 +907,6 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                     // stochastic rounding (gradients): the code of (channel r,
                     // sample n) sits at position (pix q_ncb + cb) 1024 + 32 r + n
                     // of the code tensor, which keys its random half-word
-                    const int s = (int)sc - 127;
                     const uint64_t q0 = (((uint64_t)pix * p.q_ncb + cb) * 1024 + 32 * r) >> 3;
                     const int nb = q8 ? 8 : q6 ? 6 : 4;
 #pragma unroll
@@ -918,7 +917,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                         uint32_t u = 0u;
 #pragma unroll
                         for (int t = 0; t < 4; t++)
-                            u |= encode_sr_rt(p.qfmt, v[4 * e4 + t], s, inv, rr[t]) << (nb * t);
+                            u |= encode_sr_rt(p.qfmt, v[4 * e4 + t], inv, rr[t]) << (nb * t);
                         run[e4] = bad ? 0u : u;
                     }
                 } else if (q6) {

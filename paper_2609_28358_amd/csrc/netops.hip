@@ -199,11 +199,10 @@ __global__ __launch_bounds__(256) void quantize_sum_kernel(SumArgs a, uint8_t* _
     const bool bad = sc == 0xFFu;
     uint32_t run[4];   // the codes of v[q]: channel row 8 q + lane / 8, samples j .. j + 3
     if constexpr (SR) {   // stochastic rounding, keyed by code position blk 1024 + 32 row + sample
-        const int s = (int)sc - 127;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             uint32_t cd[4];
-            sr_codes4<FMT>(v[q], (uint64_t)blk * 1024 + (8 * q + (lane >> 3)) * 32 + j, s, inv, a.k0, a.k1, cd);
+            sr_codes4<FMT>(v[q], (uint64_t)blk * 1024 + (8 * q + (lane >> 3)) * 32 + j, inv, a.k0, a.k1, cd);
             run[q] = FMT == MXC_E4M3 ? cd[0] | cd[1] << 8 | cd[2] << 16 | cd[3] << 24
                                      : cd[0] | cd[1] << 4 | cd[2] << 8 | cd[3] << 12;
         }
@@ -359,13 +358,12 @@ __global__ __launch_bounds__(256) void quantize_sum_bf_kernel(SumArgs a, uint8_t
         const int row = 16 * hh + (lane >> 2);
         uint32_t clo, chi;   // the codes of lo and hi (samples j .. j + 3, j + 4 .. j + 7)
         if constexpr (SR) {  // stochastic rounding: positions blk 1024 + 32 row + j .., one generator call
-            const int s = (int)sc - 127;
             const uint4 w = sr_words(((uint64_t)blk * 1024 + row * 32 + j) >> 3, a.k0, a.k1);
             const uint32_t r[8] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16,
                                    w.z & 0xFFFFu, w.z >> 16, w.w & 0xFFFFu, w.w >> 16};
             uint32_t cd[8];
 #pragma unroll
-            for (int e = 0; e < 8; e++) cd[e] = encode_sr<FMT>(v[hh][e], s, inv, r[e]);
+            for (int e = 0; e < 8; e++) cd[e] = encode_sr<FMT>(v[hh][e], inv, r[e]);
             constexpr int NB = FMT == MXC_E4M3 ? 8 : 4;
             clo = cd[0] | cd[1] << NB | cd[2] << (2 * NB) | cd[3] << (3 * NB);
             chi = cd[4] | cd[5] << NB | cd[6] << (2 * NB) | cd[7] << (3 * NB);
