@@ -89,6 +89,9 @@ int lean_plan(const Conv& cv, bool dg, const void* wc, const uint8_t* ws, const 
     const long long nt = count(wgm, pw, rb, true);
     if (nt <= 0 || nt > 0x7FFFFFF0LL) return 1;
     a.ntiles = (int)nt;
+    a.d_mt = make_fdiv(a.mtiles);
+    a.d_seg = make_fdiv((a.wout + px - 1) / px);
+    a.d_h = make_fdiv(a.hout);
     // stage layout: DMA slices of the weight blocks, then the halo blocks,
     // rounded to whole 4 KB groups, then the scale entries; at stride 2 the
     // widest phase has (kw + 1) / 2 taps per row

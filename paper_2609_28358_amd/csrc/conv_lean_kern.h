@@ -48,6 +48,24 @@ namespace mxc {
 #include "wgrad_tile.h"
 #include "wgrad_row.h"
 
+// Division by a launch constant as one multiplication (n below 2^31): n / d =
+// (mulhi(m, n) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d)
+// + 1 (Granlund and Montgomery, PLDI'94).  A run-time division costs a tile
+// about 25 scalar and 10 vector instructions.
+struct FDiv {
+    uint32_t m, s;
+};
+inline FDiv make_fdiv(uint32_t d) {
+    FDiv f;
+    f.s = 0;
+    while ((1ull << f.s) < d) f.s++;
+    f.m = (uint32_t)((((1ull << f.s) - d) << 32) / d + 1);
+    return f;
+}
+__device__ __forceinline__ int fdiv(int n, const FDiv& f) {
+    return (int)((__umulhi(f.m, (uint32_t)n) + (uint32_t)n) >> f.s);
+}
+
 struct LeanArgs {
     const uint8_t* wc;        // weight codes / scales
     const uint8_t* ws;
@@ -67,6 +85,7 @@ struct LeanArgs {
     int w_nco;                // weight Cout_p / 32
     int x_ncb;                // source scale blocks per pixel
     int ntiles;
+    FDiv d_mt, d_seg, d_h;    // divisions by mtiles and, outside the stride-2 input gradient, by a row's segments and hout
     int stage_bytes;          // bytes between stage buffers
     int nbuf;                 // ring depth, 2..4
     int kwf;                  // full kernel width
@@ -142,12 +161,9 @@ constexpr int LDS_MAX = 160 * 1024;       // LDS of one CU
 // instruction moves 1 KB of LDS: two FP4 blocks, or one FP8 block, or one
 // FP6 block with lane j reading the 16 bytes at 12 j (the last 4 of them
 // belong to the next half row and are never read back).
-// bf16 tiles of one output block (32 channels x 32 samples at one pixel: 2 KB
-// contiguous in the CBF layout, 64 bytes per channel row) pass through 2 KB of
-// LDS per wave, so that global memory sees whole 1 KB runs of 16 bytes per
-// lane rather than the accumulator layout's 8-byte pieces of 32 rows (twice
-// the rows touched per instruction, and four times the instructions per
-// block).  The 16-byte chunk c of row r sits at r * 64 + ((c ^ ((r / 2) % 4))
+// A bf16 z tile of one output block (32 channels x 32 samples at one pixel:
+// 2 KB contiguous in the CBF layout, 64 bytes per channel row) is read into
+// LDS in whole 1 KB runs of 16 bytes per lane.  The 16-byte chunk c of row r sits at r * 64 + ((c ^ ((r / 2) % 4))
 // * 16): rows two apart land on different chunks.
 __device__ __forceinline__ int bf16_lds(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 1) & 3)) << 4); }
 
@@ -166,24 +182,49 @@ __device__ __forceinline__ void grad_lds4(float* v, const uint8_t* zt, bool zr, 
     }
 }
 
-// Lane (r, h) = (lane % 32, lane / 32) holds samples 8 e4 + 4 h .. + 3 of row r
-// in v[4 e4 .. 4 e4 + 3] (the MFMA accumulator layout).  Rows >= rows are
-// not written.
-__device__ __forceinline__ void store_bf16_tile(uint8_t* lds, const float* v, uint16_t* dst, int rows, int lane) {
-    const int r = lane & 31, h = lane >> 5;
+// The accumulator layout leaves lane (r, h) = (lane % 32, lane / 32) with
+// samples 8 e4 + 4 h .. + 3 of row r, e4 = 0..3: the two lanes of a row hold
+// every other run of four.  v_permlane32_swap exchanges a's upper-half lanes
+// with b's lower-half ones, so two runs that far apart become two that follow
+// each other: with a = run e4 and b = run e4 + 2, lane (r, 0) gets its own and
+// its partner's run e4, lane (r, 1) its partner's and its own run e4 + 2.  Each
+// lane then holds half of the row's samples in a row and stores them straight
+// from its registers, without the instructions and the latency of a round trip
+// through LDS for every output block (measured with the codes' own: 64 -> 128,
+// stride 2, at 80x80, batch 64, the layer pass 114 -> 109 us).
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+    const auto t = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = t[0];
+    b = t[1];
+}
+// A lane index of its own for code that few calls reach: the addresses made
+// from it cannot be computed ahead of the branch, on every call's way.
+__device__ __forceinline__ int lane_here(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// One block's values v (accumulator layout) as bf16 into the CBF rows at dst;
+// rows >= rows are not written.  The whole wave must be active.
+__device__ __forceinline__ void store_bf16_tile(const float* v, uint16_t* dst, int rows, int lane) {
+    uint2 q[4];
 #pragma unroll
-    for (int e4 = 0; e4 < 4; e4++)
-        *(uint2*)(lds + bf16_lds(r, e4) + 8 * h) = bf16_pack4(v[4 * e4], v[4 * e4 + 1], v[4 * e4 + 2], v[4 * e4 + 3]);
+    for (int e4 = 0; e4 < 4; e4++) q[e4] = bf16_pack4(v[4 * e4], v[4 * e4 + 1], v[4 * e4 + 2], v[4 * e4 + 3]);
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-        const int k = lane + 64 * i, row = k >> 2, c = k & 3;
-        const uint4 d = *(const uint4*)(lds + bf16_lds(row, c));
-        if (row < rows) store_nt(dst + row * 32 + c * 8, d);
+        swap32(q[i].x, q[i + 2].x);
+        swap32(q[i].y, q[i + 2].y);
+    }
+    const int r = lane & 31;
+    if (r < rows) {
+        uint16_t* const o = dst + r * 32 + 16 * (lane >> 5);
+        store_nt(o, make_uint4(q[0].x, q[0].y, q[2].x, q[2].y));
+        store_nt(o + 8, make_uint4(q[1].x, q[1].y, q[3].x, q[3].y));
     }
 }
 
-// The inverse: z[4 e4 .. 4 e4 + 3] of lane (r, h) = samples 8 e4 + 4 h .. + 3
-// of row r of the bf16 tile at src, as floats; rows >= rows read as 0.
+// z[4 e4 .. 4 e4 + 3] of lane (r, h) = samples 8 e4 + 4 h .. + 3 of row r of
+// the bf16 tile at src, as floats, through 2 KB of LDS; rows >= rows read as 0.
 __device__ __forceinline__ void load_bf16_tile(uint8_t* lds, const uint16_t* src, int rows, int lane, float* z) {
 #pragma unroll
     for (int i = 0; i < 2; i++) {
@@ -259,11 +300,12 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
 
     // ---- tile: (row tile, pixel segment, output row of the phase, group)
     const int nseg = (f.gw + PX - 1) / PX;
-    const int mt = lin % p.mtiles;
-    int r = lin / p.mtiles;
-    const int seg = r % nseg;
-    r /= nseg;
-    const int yi = r % f.gh, g = r / f.gh;
+    int r = fdiv(lin, p.d_mt);
+    const int mt = lin - r * p.mtiles;
+    const int rs = DS == 1 ? fdiv(r, p.d_seg) : r / nseg;
+    const int seg = r - rs * nseg;
+    const int g = DS == 1 ? fdiv(rs, p.d_h) : rs / f.gh;
+    const int yi = rs - g * f.gh;
     const int x0 = seg * PX;                                       // first pixel on the phase grid
     const int cbase = DG ? x0 + f.c0 - (KW - 1) : x0 * S - p.pw;   // first halo column
 
@@ -302,7 +344,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
         } else if (slice < NSW + NSX) {
             // [K half kb][halo pixel hc]
             const int b = (slice - NSW) * BX::BPI + (BX::BPI == 2 ? (lane >> 5) : 0);
-            const int kb = b / HP, hc = b % HP;
+            const int kb = b >= HP ? 1 : 0, hc = b - kb * HP;
             const int col = cbase + hc;
             const bool ok = col >= 0 && col < p.wsrc;
             // channel rows past a single block's real channels hold +0 codes:
@@ -328,7 +370,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
         if (KR) s_off += (uint32_t)(kb * DS) * p.kwf * p.w_ncb;
         s_flg = (rowblk < p.w_rowblocks ? 1u : 0u) | (uint32_t)kb << 1 | 8u;
     } else if (tid < NSA + NSB) {
-        const int q = tid - NSA, kb = q / HP, hc = q % HP;
+        const int q = tid - NSA, kb = q >= HP ? 1 : 0, hc = q - kb * HP;
         const int col = cbase + hc;
         const bool ok = col >= 0 && col < p.wsrc;
         s_off = (uint32_t)(ok ? col : 0) * p.x_ncb + (KR ? 0u : (uint32_t)kb);
@@ -386,7 +428,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
         const uint32_t okm = (ok0 ? 1u : 0u) | (ok1 ? 2u : 0u) | 4u | (has1 ? 8u : 0u);
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
-            const bool isb = flg[q] & 4u;
+            const bool isb = 4 * q + wave >= NSW;   // an activation slice (uniform over the wave)
             const bool ok = (okm & need[q]) != 0u;
             const uint8_t* src = isb ? p.sc + (xrow + off[q]) : abase + off[q];
             dma16_async(ok ? src : zero + (isb ? in_x : in_w), lds_addr(lds + (4 * q + wave) * 1024));
@@ -417,7 +459,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
         const uint32_t okm = 1u | (kb1_ok ? 2u : 0u) | (row_ok ? 4u : 0u);
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
-            const bool isb = flg[q] & 4u;
+            const bool isb = 4 * q + wave >= NSW;   // an activation slice (uniform over the wave)
             const bool ok = (okm & need[q]) == need[q];
             const uint8_t* src = (isb ? bbase : abase) + off[q];
             dma16_async(ok ? src : zero + (isb ? in_x : in_w), lds_addr(lds + (4 * q + wave) * 1024));
@@ -703,7 +745,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
 #pragma unroll
                 for (int e = 0; e < 16; e++) acc[rb][cn][e] *= tt;
     }
-    if (p.layout != MXC_NCHW && !(Q && p.qcodes))
+    if (p.layout == MXC_CBF && !(Q && p.qcodes))
         __syncthreads();                                 // every wave is done with the stage buffers
     uint8_t* const ep = smem + wave * 4096;
     const int er = lane >> 3, ec = lane & 7;            // read-back: row er + 8 i, chunk ec
@@ -712,10 +754,12 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
     if (Q && p.qcodes) {
         // ---- fused quantizing epilogue: acc[rb][cn] is one whole MX block of
         // the output (32 channels x 32 samples at one pixel); lane l holds
-        // channel l % 32 and samples 8 (e / 4) + 4 (l / 32) + e % 4.  The
-        // codes are assembled in 1 KB of LDS per wave in stored order and
-        // written as one contiguous run (16 or 8 bytes per lane).
-        __syncthreads();                                 // every wave is done with the stage buffers
+        // channel l % 32 and samples 8 (e / 4) + 4 (l / 32) + e % 4.  FP8 /
+        // FP4 codes and bf16 values leave from registers (swap32); FP6 codes,
+        // fp32 values and z tiles that were not prefetched pass through LDS,
+        // once every wave is done with the stage buffers.
+        if (p.qfmt == MXC_E2M3 || p.qfmt == MXC_E3M2 || (p.out && !(p.bf16 && p.pre_out)) || (DG && !zpf))
+            __syncthreads();
         uint8_t* const ep = smem + wave * 1024;
         const int r = lane & 31;
         // the fp32 output of one block (32 channels x 32 samples, 4 KB
@@ -723,6 +767,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
         // XOR-swizzled by row) and out as four whole 1 KB non-temporal runs
         uint8_t* const ep4 = smem + 4096 + wave * 4096;
         auto store_block = [&](const float* val, size_t pix, int cb) {
+            const int l = lane_here(lane), r = l & 31, h = l >> 5, er = l >> 3, ec = l & 7;
 #pragma unroll
             for (int e4 = 0; e4 < 4; e4++)
                 *(float4*)(ep4 + r * 128 + (((2 * e4 + h) ^ (r & 7)) << 4)) =
@@ -783,15 +828,15 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                     // the values of one block through LDS to global memory:
                     // bf16 (2 KB, 64-byte rows) or fp32 (4 KB, 128-byte rows)
                     auto stage_out = [&](const float* w, bool as_bf16, void* dst) {
-                        if (as_bf16) {
-#pragma unroll
-                            for (int k = 0; k < 2; k++)
-                                *(uint2*)(ep4 + bf16_lds(row, k0 + k) + 8 * h) =
-                                    bf16_pack4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-                            const int rr = lane >> 2, ch = lane & 3;      // rows 0..15: one chunk per lane
-                            const uint4 d = *(const uint4*)(ep4 + bf16_lds(rr, ch));
-                            if (rr < rows) store_nt((uint16_t*)dst + rr * 32 + ch * 8, d);
+                        if (as_bf16) {   // runs k0, k0 + 1: run k0 + h of both lanes of the row, 16 bytes
+                            uint2 a = bf16_pack4(w[0], w[1], w[2], w[3]), b = bf16_pack4(w[4], w[5], w[6], w[7]);
+                            swap32(a.x, b.x);
+                            swap32(a.y, b.y);
+                            if (row < rows)
+                                store_nt((uint16_t*)dst + row * 32 + 8 * (k0 + h), make_uint4(a.x, a.y, b.x, b.y));
                         } else {
+                            const int l = lane_here(lane), row = l & 15, k0 = ((l >> 4) & 1) * 2, h = l >> 5, er = l >> 3,
+                                      ec = l & 7;
 #pragma unroll
                             for (int k = 0; k < 2; k++)
                                 *(float4*)(ep4 + row * 128 + (((2 * (k0 + k) + h) ^ (row & 7)) << 4)) =
@@ -821,29 +866,29 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                     const float inv = inv_scale(sc);
                     const bool bad = sc == 0xFFu;
                     if (lane == 0) p.qscales[pix * p.q_ncb + cb] = (uint8_t)sc;
-                    if (q8) {   // 32-byte rows; rows 16..31 are +0 codes
-#pragma unroll
-                        for (int k = 0; k < 2; k++)
-                            *(uint32_t*)(ep + row * 32 + 8 * (k0 + k) + 4 * h) =
-                                bad ? 0u : pack4_e4m3(make_float4(u[4 * k], u[4 * k + 1], u[4 * k + 2], u[4 * k + 3]), inv);
-                        *(uint2*)(ep + 512 + 8 * lane) = make_uint2(0u, 0u);
-                        const uint4 chunk = *(const uint4*)(ep + lane * 16);
-                        *(uint4*)(p.qcodes + (pix * p.q_ncb + cb) * 1024 + lane * 16) = chunk;
-                    } else {    // 16-byte rows
-#pragma unroll
-                        for (int k = 0; k < 2; k++)
-                            *(unsigned short*)(ep + row * 16 + 4 * (k0 + k) + 2 * h) =
-                                bad ? (unsigned short)0
-                                    : pack4_e2m1(make_float4(u[4 * k], u[4 * k + 1], u[4 * k + 2], u[4 * k + 3]), inv);
-                        *(uint32_t*)(ep + 256 + 4 * lane) = 0u;
-                        const uint2 chunk = *(const uint2*)(ep + lane * 8);
-                        *(uint2*)(p.qcodes + (pix * p.q_ncb + cb) * 512 + lane * 8) = chunk;
+                    const size_t blk = pix * p.q_ncb + cb;
+                    if (q8) {   // 32-byte rows, 8 bytes per lane; rows 16..31 are +0 codes
+                        uint32_t c0 = pack4_e4m3(make_float4(u[0], u[1], u[2], u[3]), inv);
+                        uint32_t c1 = pack4_e4m3(make_float4(u[4], u[5], u[6], u[7]), inv);
+                        swap32(c0, c1);
+                        uint8_t* const o = p.qcodes + blk * 1024;
+                        *(uint2*)(o + row * 32 + 8 * (k0 + h)) = bad ? make_uint2(0u, 0u) : make_uint2(c0, c1);
+                        *(uint2*)(o + 512 + 8 * lane) = make_uint2(0u, 0u);
+                    } else {    // 16-byte rows, 4 bytes per lane
+                        // both runs of both lanes of the row: h = 0 keeps the low halves, h = 1 the high ones
+                        uint32_t c0 = pack8_e2m1(make_float4(u[0], u[1], u[2], u[3]), make_float4(u[4], u[5], u[6], u[7]),
+                                                 inv), c1 = c0;
+                        swap32(c0, c1);
+                        const uint32_t w = __builtin_amdgcn_perm(c1, c0, h ? 0x07060302u : 0x05040100u);
+                        uint8_t* const o = p.qcodes + blk * 512;
+                        *(uint32_t*)(o + row * 16 + 4 * (k0 + h)) = bad ? 0u : w;
+                        *(uint32_t*)(o + 256 + 4 * lane) = 0u;
                     }
                     continue;
                 }
                 if (p.bf16) to_bf16(v, 16);
                 if (p.out && p.pre_out) {   // the pre-activation, for the backward pass
-                    if (p.bf16) store_bf16_tile(ep4, v, (uint16_t*)p.out + (pix * p.M + (size_t)cb * 32) * 32, rows, lane);
+                    if (p.bf16) store_bf16_tile(v, (uint16_t*)p.out + (pix * p.M + (size_t)cb * 32) * 32, rows, lane);
                     else        store_block(v, pix, cb);
                 }
                 // The activation (forward) or its derivative at z (input
@@ -943,6 +988,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                 }
                 if (q6) {
                     // 24 bits per run, stored at byte 6 e4 + 3 h of the channel's 24-byte row
+                    const int lane_q = lane_here(lane), r = lane_q & 31, h = lane_q >> 5;
 #pragma unroll
                     for (int e4 = 0; e4 < 4; e4++) {
                         uint8_t* d = ep + r * 24 + 6 * e4 + 3 * h;
@@ -954,16 +1000,16 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                         const uint4 chunk = *(const uint4*)(ep + lane * 16);
                         *(uint4*)(p.qcodes + (pix * p.q_ncb + cb) * 768 + lane * 16) = chunk;
                     }
-                } else if (q8) {
-#pragma unroll
-                    for (int e4 = 0; e4 < 4; e4++) *(uint32_t*)(ep + r * 32 + 8 * e4 + 4 * h) = run[e4];
-                    const uint4 chunk = *(const uint4*)(ep + lane * 16);
-                    *(uint4*)(p.qcodes + (pix * p.q_ncb + cb) * 1024 + lane * 16) = chunk;
-                } else {
-#pragma unroll
-                    for (int e4 = 0; e4 < 4; e4++) *(unsigned short*)(ep + r * 16 + 4 * e4 + 2 * h) = (unsigned short)run[e4];
-                    const uint2 chunk = *(const uint2*)(ep + lane * 8);
-                    *(uint2*)(p.qcodes + (pix * p.q_ncb + cb) * 512 + lane * 8) = chunk;
+                } else if (q8) {   // 32-byte rows, 16 bytes per lane
+                    swap32(run[0], run[2]);
+                    swap32(run[1], run[3]);
+                    *(uint4*)(p.qcodes + (pix * p.q_ncb + cb) * 1024 + r * 32 + 16 * h) =
+                        make_uint4(run[0], run[2], run[1], run[3]);
+                } else {           // 16-byte rows, 8 bytes per lane
+                    uint32_t lo = run[0] | run[1] << 16, hi = run[2] | run[3] << 16;
+                    swap32(lo, hi);
+                    *(uint2*)(p.qcodes + (pix * p.q_ncb + cb) * 512 + r * 16 + 8 * h) =
+                        make_uint2(__builtin_amdgcn_perm(hi, lo, 0x05040100u), __builtin_amdgcn_perm(hi, lo, 0x07060302u));
                 }
             }
         }
@@ -1016,7 +1062,7 @@ __device__ __forceinline__ void lean_tile(const LeanArgs& p, int lin, const Phas
                 float v[16];
 #pragma unroll
                 for (int e = 0; e < 16; e++) v[e] = acc[rb][cn][e];
-                store_bf16_tile(ep, v, px + (size_t)m0 * 32, min(32, p.M - m0), lane);
+                store_bf16_tile(v, px + (size_t)m0 * 32, min(32, p.M - m0), lane);
             }
         } else {
             float* px = p.out + (((size_t)g * p.hout + y) * p.wout + x) * p.M * 32;
