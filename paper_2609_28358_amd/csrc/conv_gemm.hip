@@ -624,92 +624,96 @@ __global__ __launch_bounds__(NT) void wgrad_kernel(WgradArgs p) {
 }
 
 // G_W[co][ci][kh][kw] = sum over splits of the partial (co, tap*Cin_p + ci).
-// Below 64 splits a thread takes a column and keeps four sums, sum q adding
-// splits q, q + 4, q + 8, ... in increasing order, and returns (sum0 + sum1)
-// + (sum2 + sum3).  From 64 splits on (the first layers: few columns, many
-// splits, where a thread per column left most of the GPU idle behind long
-// load chains) sixteen threads share a column: thread q adds splits q, q +
-// 16, ... in increasing order and the column's result is the pairwise tree
-// ((s0 + s1) + (s2 + s3)) + ... of the sixteen.  Either way a fixed order:
-// the result does not depend on timing, and the same bits whether one layer
-// or several are reduced by the launch.  A workgroup takes 256 / nr
-// consecutive columns (nr = 1 or 16); neighbouring threads read
-// neighbouring columns of one split.
+// Below 64 splits four threads share a column, thread q adding splits q,
+// q + 4, ... in increasing order; from 64 splits on (the first layers: few
+// columns, many splits) sixteen do, thread q adding splits q, q + 16, ...;
+// the column's result is the pairwise tree ((s0 + s1) + (s2 + s3)) + ... of
+// them.  Either way a fixed order: the result does not depend on timing, and
+// the same bits whether one layer or several are reduced by the launch.  A
+// thread takes four neighbouring columns (16-byte loads; a row of columns is a
+// multiple of 32 floats), a workgroup 256 or 64.  It reads each partial sum
+// once and nothing twice, so HBM bounds it; one column per thread with run-time
+// divisions (two of them 64 bits wide, for an index that is its own result)
+// and jobs selected field by field kept the vector and scalar units busy for
+// longer than that (the network step, batch 64: 329 MB, two launches, 107 -> 68 us).
 struct RedGeom {
-    int cout, cin, kh, kw, gy_cp, x_cp, ntot, splits, nr;
+    int cin, khkw, x_cp, ntot, splits;
+    FDiv d_ntot, d_xcp;               // divisions by ntot and x_cp
+    long cols;                        // cout * ntot, a multiple of 32
+    size_t stride;                    // floats between splits
 };
 
-inline int reduce_nr(int splits) { return splits >= 64 ? 16 : 1; }
+constexpr int NR_FEW = 4, NR_MANY = 16;                   // threads that share a column
+inline int reduce_nr(int splits) { return splits >= 64 ? NR_MANY : NR_FEW; }
 
 __device__ __forceinline__ void reduce_store(float* __restrict__ gw, const RedGeom& r, long i, float sum) {
-    const int co = (int)(i / r.ntot), col = (int)(i % r.ntot);
-    const int tap = col / r.x_cp, ci = col % r.x_cp;
-    if (ci < r.cin)
-        gw[(((size_t)co * r.cin + ci) * r.kh + tap / r.kw) * r.kw + tap % r.kw] = sum;
+    int co, tap;
+    if (i < 0x7FFFFFFFL) co = fdiv((int)i, r.d_ntot);
+    else                 co = (int)(i / r.ntot);
+    const int col = (int)(i - (long)co * r.ntot);
+    tap = fdiv(col, r.d_xcp);
+    const int ci = col - tap * r.x_cp;
+    if (ci < r.cin) gw[((size_t)co * r.cin + ci) * r.khkw + tap] = sum;
 }
 
-__device__ __forceinline__ void reduce_cols(const float* __restrict__ part, float* __restrict__ gw,
-                                            const RedGeom& r, long wg) {
-    const size_t stride = (size_t)r.gy_cp * r.ntot;
-    if (r.nr == 1) {
-        const long i = wg * 256 + threadIdx.x;
-        if (i >= (long)r.cout * r.ntot) return;
-        const float* q = part + (size_t)(i / r.ntot) * r.ntot + (i % r.ntot);
-        float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        int k = 0;
-        for (; k + 8 <= r.splits; k += 8) {                 // eight loads in flight
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = __ldg(q + (size_t)(k + j) * stride);
-#pragma unroll
-            for (int j = 0; j < 8; j++) a[j & 3] += v[j];
-        }
-        for (; k < r.splits; k++) a[k & 3] += __ldg(q + (size_t)k * stride);
-        reduce_store(gw, r, i, (a[0] + a[1]) + (a[2] + a[3]));
-        return;
-    }
-    __shared__ float red[256];
-    constexpr int NR = 16, PER = 256 / NR;
-    const int t = threadIdx.x, qi = t / PER, cl = t % PER;
-    const long i = wg * PER + cl;
-    const bool live = i < (long)r.cout * r.ntot;
-    float a = 0.0f;
-    if (live) {
-        const float* q = part + (size_t)(i / r.ntot) * r.ntot + (i % r.ntot);
+// NR threads per column, each four columns wide (16-byte loads).
+template <int NR>
+__device__ __forceinline__ void reduce_cols_nr(const float* __restrict__ part, float* __restrict__ gw,
+                                               const RedGeom& r, long wg, float* red) {
+    constexpr int TC = 256 / NR, COLS = 4 * TC;
+    const int t = threadIdx.x, qi = t / TC, cl = 4 * (t % TC);
+    const long i0 = wg * COLS;
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (i0 + cl < r.cols) {
+        const float* q = part + i0 + cl + (size_t)qi * r.stride;
+        const size_t step = NR * r.stride;
         int k = qi;
-        for (; k + 7 * NR < r.splits; k += 8 * NR) {        // eight loads in flight
-            float v[8];
+        for (; k + 3 * NR < r.splits; k += 4 * NR) {        // four loads in flight
+            float4 v[4];
 #pragma unroll
-            for (int j = 0; j < 8; j++) v[j] = __ldg(q + (size_t)(k + j * NR) * stride);
+            for (int j = 0; j < 4; j++, q += step) v[j] = __ldg((const float4*)q);
 #pragma unroll
-            for (int j = 0; j < 8; j++) a += v[j];
+            for (int j = 0; j < 4; j++) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
         }
-        for (; k < r.splits; k += NR) a += __ldg(q + (size_t)k * stride);
+        for (; k < r.splits; k += NR, q += step) {
+            const float4 v = __ldg((const float4*)q);
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
     }
-    red[t] = a;
+    *(float4*)(red + qi * COLS + cl) = a;
     __syncthreads();
-    if (qi != 0 || !live) return;
+    if (t >= COLS || i0 + t >= r.cols) return;
     float s[NR];
 #pragma unroll
-    for (int j = 0; j < NR; j++) s[j] = red[j * PER + cl];
+    for (int j = 0; j < NR; j++) s[j] = red[j * COLS + t];
 #pragma unroll
     for (int w = 1; w < NR; w *= 2)                         // pairwise tree
 #pragma unroll
         for (int j = 0; j + w < NR; j += 2 * w) s[j] = s[j] + s[j + w];
-    reduce_store(gw, r, i, s[0]);
+    reduce_store(gw, r, i0 + t, s[0]);
+}
+
+__device__ __forceinline__ void reduce_cols(const float* __restrict__ part, float* __restrict__ gw,
+                                            const RedGeom& r, long wg) {
+    __shared__ __attribute__((aligned(16))) float red[1024];
+    if (r.splits >= 64) reduce_cols_nr<NR_MANY>(part, gw, r, wg, red);
+    else                reduce_cols_nr<NR_FEW>(part, gw, r, wg, red);
 }
 
 // workgroups of one reduction
 long reduce_wgs(const Conv& cv, int splits) {
-    const long per = 256 / reduce_nr(splits);
+    const long per = 1024 / reduce_nr(splits);
     return ((long)cv.cout * cv.kh * cv.kw * cv.x.cp + per - 1) / per;
 }
 
 RedGeom red_geom(const Conv& cv, int splits) {
     RedGeom r;
-    r.cout = cv.cout; r.cin = cv.cin; r.kh = cv.kh; r.kw = cv.kw;
-    r.gy_cp = cv.gy.cp; r.x_cp = cv.x.cp; r.ntot = cv.kh * cv.kw * cv.x.cp; r.splits = splits;
-    r.nr = reduce_nr(splits);
+    r.cin = cv.cin; r.khkw = cv.kh * cv.kw;
+    r.x_cp = cv.x.cp; r.ntot = cv.kh * cv.kw * cv.x.cp; r.splits = splits;
+    r.d_ntot = make_fdiv((uint32_t)r.ntot);
+    r.d_xcp = make_fdiv((uint32_t)r.x_cp);
+    r.cols = (long)cv.cout * r.ntot;
+    r.stride = (size_t)cv.gy.cp * r.ntot;
     return r;
 }
 
@@ -719,15 +723,16 @@ __global__ __launch_bounds__(256) void wgrad_reduce(const float* __restrict__ pa
 }
 
 // Several layers' reductions in one launch: the workgroups of job i take
-// [wg0_i, wg0_i + reduce_wgs(job i)); the job is picked with scalar
-// selects, as in the batched quantizer.
+// [wg0[i], wg0[i + 1]).  The job's index is found in scalar registers and its
+// arguments loaded by it (selecting them job by job was about 600 scalar
+// instructions of every wave).
 struct RJob {
     const float* part;
     float* gw;
     RedGeom r;
-    int wg0;
 };
 struct RMulti {
+    int wg0[MXC_WREDUCE_MAX];
     RJob j[MXC_WREDUCE_MAX];
     int count, nwg;
 };
@@ -735,11 +740,11 @@ struct RMulti {
 __global__ __launch_bounds__(256) void wgrad_reduce_multi(RMulti m) {
     const int wg = (int)blockIdx.x;
     if (wg >= m.nwg) return;                                      // the whole workgroup
-    RJob q = m.j[0];
+    int k = 0;
 #pragma unroll
-    for (int t = 1; t < MXC_WREDUCE_MAX; t++)
-        if (t < m.count && wg >= m.j[t].wg0) q = m.j[t];
-    reduce_cols(q.part, q.gw, q.r, wg - q.wg0);
+    for (int t = 1; t < MXC_WREDUCE_MAX; t++) k += wg >= m.wg0[t] ? 1 : 0;   // wg0 past the last job: nwg
+    const RJob& q = m.j[k];
+    reduce_cols(q.part, q.gw, q.r, wg - m.wg0[k]);
 }
 
 int launch_reduce(const Conv& cv, const float* part, float* gw, int splits, hipStream_t s) {
@@ -1535,14 +1540,15 @@ int launch_wgrad_reduce_multi(int count, const WReduceJob* jobs, hipStream_t s) 
         if (splits == 0) continue;                        // G_W was written by the weight-gradient kernel
         const long wgs = reduce_wgs(jobs[i].cv, splits);
         if (nwg + wgs > 0x7FFFFFFFL) return MXC_ERR_SHAPE;
+        m.wg0[nq] = (int)nwg;
         RJob& d = m.j[nq++];
-        d.part = (const float*)jobs[i].ws; d.gw = jobs[i].gw; d.r = red_geom(jobs[i].cv, splits); d.wg0 = (int)nwg;
+        d.part = (const float*)jobs[i].ws; d.gw = jobs[i].gw; d.r = red_geom(jobs[i].cv, splits);
         nwg += wgs;
     }
     if (nq == 0) return MXC_OK;
     m.count = nq;
     m.nwg = (int)nwg;
-    for (int i = nq; i < MXC_WREDUCE_MAX; i++) m.j[i] = m.j[nq - 1];
+    for (int i = nq; i < MXC_WREDUCE_MAX; i++) { m.wg0[i] = m.nwg; m.j[i] = m.j[nq - 1]; }
     hipLaunchKernelGGL(wgrad_reduce_multi, dim3((unsigned)nwg), dim3(256), 0, s, m);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }

@@ -48,24 +48,6 @@ namespace mxc {
 #include "wgrad_tile.h"
 #include "wgrad_row.h"
 
-// Division by a launch constant as one multiplication (n below 2^31): n / d =
-// (mulhi(m, n) + n) >> s with s = ceil(log2 d), m = floor(2^32 (2^s - d) / d)
-// + 1 (Granlund and Montgomery, PLDI'94).  A run-time division costs a tile
-// about 25 scalar and 10 vector instructions.
-struct FDiv {
-    uint32_t m, s;
-};
-inline FDiv make_fdiv(uint32_t d) {
-    FDiv f;
-    f.s = 0;
-    while ((1ull << f.s) < d) f.s++;
-    f.m = (uint32_t)((((1ull << f.s) - d) << 32) / d + 1);
-    return f;
-}
-__device__ __forceinline__ int fdiv(int n, const FDiv& f) {
-    return (int)((__umulhi(f.m, (uint32_t)n) + (uint32_t)n) >> f.s);
-}
-
 struct LeanArgs {
     const uint8_t* wc;        // weight codes / scales
     const uint8_t* ws;
