@@ -684,7 +684,7 @@ def sweep_leg(args):
                     raise mx.MxconvError(mx.strerror(c))
 
             kq = max(12, len(xsrc), len(gsrc))
-            ws4 = torch.empty(max(1, mx.wgrad_workspace_bytes(cv, 1)), dtype=torch.uint8, device=dev)
+            ws4 = torch.empty(max(1, mx.nvfp_wgrad_workspace_bytes(cv, 1)), dtype=torch.uint8, device=dev)
             t = {"quant_x": steady_ms(lambda: nq(qx, xsrc, "x", j["xs"]), kq),
                  "quant_w": steady_ms(lambda: mx.nvfp_quantize(j["w"], mx.WEIGHT, 1, workspace=wsn)),
                  "quant_gy": steady_ms(lambda: nq(qg, gsrc, "g", j["gs"]), kq),
@@ -703,7 +703,7 @@ def sweep_leg(args):
                 mw = mx.nvfp_quantize(j["w"], mx.WEIGHT, fw_, workspace=wsn)
                 mxq = mx.nvfp_quantize(j["x"], mx.ACT, fx_, layout=mx.CBF, shape=j["xs"], workspace=wsn)
                 mg = mx.nvfp_quantize(j["gy"], mx.ACT, fg_, layout=mx.CBF, shape=j["gs"], workspace=wsn)
-                wsm = torch.empty(max(1, mx.wgrad_workspace_bytes(cv, mx.pair(fg_, fx_))), dtype=torch.uint8,
+                wsm = torch.empty(max(1, mx.nvfp_wgrad_workspace_bytes(cv, mx.pair(fg_, fx_))), dtype=torch.uint8,
                                   device=dev)
                 tm = {"fwd": steady_ms(lambda: mx.nvfp_fwd(cv, mw, mxq, layout=mx.CBF, out=j["y"])),
                       "dgrad": steady_ms(lambda: mx.nvfp_dgrad(cv, mw, mg, layout=mx.CBF, out=j["gx"])),

@@ -279,7 +279,10 @@ int mxconv_nvfp_quantize(const void* src, int dtype, int layout, int role, int f
  * (W, X / W, G_Y / G_Y, X); other pairs return MXC_ERR_ARG.  Layers outside
  * the batch-block-32 kernels (kernel width 1 or 3, forward column stride 1
  * or 2, input-gradient stride 1x1 or 2x2) return MXC_ERR_SHAPE.  The weight
- * gradient uses the workspace of mxconv_wgrad_workspace_bytes(cv, fmt).
+ * gradient's workspace has mxconv_nvfp_wgrad_workspace_bytes(cv, fmt) bytes
+ * (0 for what the call refuses); it also runs in the workspace of the layer's
+ * MX form, mxconv_wgrad_workspace_bytes(cv, fmt), which may be smaller: fewer
+ * partial sums, and slower.
  * Errors: NULL, ARG, SHAPE, ALIGN, WORKSPACE, HIP. */
 int mxconv_nvfp_fwd(const mxc_conv* cv, int fmt,
                     const void* w_codes, const uint8_t* w_scales, const float* w_t,
@@ -289,6 +292,7 @@ int mxconv_nvfp_dgrad(const mxc_conv* cv, int fmt,
                       const void* w_codes, const uint8_t* w_scales, const float* w_t,
                       const void* gy_codes, const uint8_t* gy_scales, const float* gy_t,
                       float* gx, int gx_layout, void* stream);
+size_t mxconv_nvfp_wgrad_workspace_bytes(const mxc_conv* cv, int fmt);
 int mxconv_nvfp_wgrad(const mxc_conv* cv, int fmt,
                       const void* gy_codes, const uint8_t* gy_scales, const float* gy_t,
                       const void* x_codes, const uint8_t* x_scales, const float* x_t,

@@ -1461,25 +1461,26 @@ static int bn32_splits(const Conv& cv) {
     return rs > 0 ? rs : ls;
 }
 
+// bytes of `splits` partial results of a batch-block-32 kernel (one: G_W itself)
+static size_t partial_bytes(const Conv& cv, int splits) {
+    return splits > 1 ? (size_t)splits * cv.gy.cp * cv.kh * cv.kw * cv.x.cp * sizeof(float) : 0;
+}
+
 size_t wgrad_workspace(const Conv& cv) {
     const int sp = bn32_splits(cv);
-    if (sp > 0) return sp > 1 ? (size_t)sp * cv.gy.cp * cv.kh * cv.kw * cv.x.cp * sizeof(float) : 0;
+    if (sp > 0) return partial_bytes(cv, sp);
     if (!general_fmt(cv)) return 0;
     const WgradPlan pl = wgrad_plan(cv);
     return (size_t)pl.splits * cv.gy.cp * pl.ntot * sizeof(float);
 }
 
 int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc, const uint8_t* xs,
-                 float* gw, void* ws, hipStream_t s, const float* nv_tg, const float* nv_tx, bool defer) {
-    int sp = bn32_splits(cv);
-    if (nv_tg && sp == 0) return MXC_ERR_SHAPE;
+                 float* gw, void* ws, hipStream_t s, bool defer) {
+    const int sp = bn32_splits(cv);
     if (sp > 0) {
-        // NVFP operands run the lean kernel, within the workspace of the layer's MX form
-        if (nv_tg) sp = std::min(sp, wgrad_lean_splits(cv));
         float* const dst = sp > 1 ? (float*)ws : gw;
-        const int rc = !nv_tg && wgrad_row_splits(cv) > 0
-                           ? launch_wgrad_row(cv, gc, gs, xc, xs, dst, s)
-                           : launch_wgrad_lean(cv, gc, gs, xc, xs, dst, sp, s, nv_tg, nv_tx);
+        const int rc = wgrad_row_splits(cv) > 0 ? launch_wgrad_row(cv, gc, gs, xc, xs, dst, s)
+                                                : launch_wgrad_lean(cv, gc, gs, xc, xs, dst, sp, s);
         if (rc || sp == 1 || defer) return rc;
         return launch_reduce(cv, (const float*)ws, gw, sp, s);
     }
@@ -1509,6 +1510,22 @@ int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* 
     return launch_reduce(cv, (const float*)ws, gw, pl.splits, s);
 }
 
+// The MX form's count suits the kernel-row tile, which takes three taps: up to
+// a third fewer workgroups of the one-tap tile than fill the GPU (NVFP8
+// 64 -> 64 at 56x56, batch 64: 50.5 us with its own count, 64.7 with the MX one).
+size_t nvfp_wgrad_workspace(const Conv& cv) { return partial_bytes(cv, wgrad_lean_splits(cv, true)); }
+
+int launch_nvfp_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const float* tg, const void* xc,
+                      const uint8_t* xs, const float* tx, float* gw, void* ws, size_t ws_bytes, hipStream_t s) {
+    int sp = wgrad_lean_splits(cv, true);
+    if (sp == 0) return MXC_ERR_SHAPE;
+    if (ws_bytes < partial_bytes(cv, sp)) sp = std::min(sp, bn32_splits(cv));
+    if (ws_bytes < partial_bytes(cv, sp)) return MXC_ERR_WORKSPACE;
+    const int rc = launch_wgrad_lean(cv, gc, gs, xc, xs, sp > 1 ? (float*)ws : gw, sp, s, tg, tx);
+    if (rc || sp == 1) return rc;
+    return launch_reduce(cv, (const float*)ws, gw, sp, s);
+}
+
 int launch_backward(const Conv& dcv, const void* wc, const uint8_t* ws, const void* gc, const uint8_t* gs,
                     float* gx, int layout, const Conv& wcv, const void* xc, const uint8_t* xs, float* gw,
                     void* wsp, hipStream_t s, bool defer) {
@@ -1522,7 +1539,7 @@ int launch_backward(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     }
     const int rc = launch_dgrad(dcv, wc, ws, gc, gs, gx, layout, s);
     if (rc) return rc;
-    return launch_wgrad(wcv, gc, gs, xc, xs, gw, wsp, s, nullptr, nullptr, defer);
+    return launch_wgrad(wcv, gc, gs, xc, xs, gw, wsp, s, defer);
 }
 
 int wgrad_pending_splits(const Conv& cv) {

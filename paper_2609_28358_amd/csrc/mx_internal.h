@@ -124,8 +124,8 @@ int launch_backward(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
                     void* wsp, hipStream_t s, bool defer);
 // weight gradient for batch block 32 (wgrad_lean.hip): number of K splits
 // (0: not applicable); with more than one split the partial tiles go to the
-// workspace and are reduced by the caller
-int wgrad_lean_splits(const Conv& cv);
+// workspace and are reduced by the caller; nv: with NVFP operands
+int wgrad_lean_splits(const Conv& cv, bool nv = false);
 // the batch-block-32 weight gradient on 32 x 32 tiles: G_Y and X each a
 // single channel block, formats MXFP8 or MXFP4
 inline bool wgrad_single_block(const Conv& cv) {
@@ -147,8 +147,13 @@ int launch_wgrad_row(const Conv& cv, const void* gc, const uint8_t* gs, const vo
                      hipStream_t s);
 size_t wgrad_workspace(const Conv& cv);
 int launch_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const void* xc,
-                 const uint8_t* xs, float* gw, void* ws, hipStream_t s, const float* nv_tg = nullptr,
-                 const float* nv_tx = nullptr, bool defer = false);
+                 const uint8_t* xs, float* gw, void* ws, hipStream_t s, bool defer = false);
+// NVFP operands: the one-tap kernel (wgrad_lean.hip), split as its own tile
+// wants it (nvfp_wgrad_workspace), or, in a workspace that holds less, as the
+// layer's MX form is split
+size_t nvfp_wgrad_workspace(const Conv& cv);
+int launch_nvfp_wgrad(const Conv& cv, const void* gc, const uint8_t* gs, const float* tg, const void* xc,
+                      const uint8_t* xs, const float* tx, float* gw, void* ws, size_t ws_bytes, hipStream_t s);
 // Split-K partial sums a deferred weight gradient leaves in its workspace
 // (0: the kernel wrote G_W itself), and their reduction for several layers.
 int wgrad_pending_splits(const Conv& cv);

@@ -126,6 +126,12 @@ size_t mxconv_wgrad_workspace_bytes(const mxc_conv* p, int fmt) {
     return wgrad_workspace(cv);
 }
 
+size_t mxconv_nvfp_wgrad_workspace_bytes(const mxc_conv* p, int fmt) {
+    Conv cv;
+    if (!p || conv_init(&cv, p, fmt, CONV_WGRAD) || !nv_pair_ok(cv.fa, cv.fb)) return 0;
+    return nvfp_wgrad_workspace(cv);
+}
+
 int mxconv_quantize(const void* src, int dtype, int layout, int role, int fmt, int n, int c,
                     int h, int w, void* codes, uint8_t* scales, void* stream) {
     if (!src || !codes || !scales) return MXC_ERR_NULL;
@@ -250,13 +256,14 @@ int mxconv_nvfp_wgrad(const mxc_conv* p, int fmt, const void* gc, const uint8_t*
     int rc = conv_init(&cv, p, fmt, CONV_WGRAD);
     if (rc) return rc;
     if (!nv_pair_ok(cv.fa, cv.fb)) return MXC_ERR_ARG;
-    if (wgrad_lean_splits(cv) == 0) return MXC_ERR_SHAPE;
-    const size_t need = wgrad_workspace(cv);
-    if (need && (!workspace || ws_bytes < need)) return MXC_ERR_WORKSPACE;
+    if (wgrad_lean_splits(cv, true) == 0) return MXC_ERR_SHAPE;
+    const size_t own = nvfp_wgrad_workspace(cv), need = std::min(own, wgrad_workspace(cv));
+    if (!workspace) ws_bytes = 0;
+    if (ws_bytes < need) return MXC_ERR_WORKSPACE;
     if (!aligned16(gc) || !aligned16(gs) || !aligned16(gt) || !aligned16(xc) || !aligned16(xs) ||
-        !aligned16(xt) || !aligned16(gw) || (need && !aligned16(workspace)))
+        !aligned16(xt) || !aligned16(gw) || ((need || (own && ws_bytes >= own)) && !aligned16(workspace)))
         return MXC_ERR_ALIGN;
-    return launch_wgrad(cv, gc, gs, xc, xs, gw, workspace, (hipStream_t)stream, gt, xt);
+    return launch_nvfp_wgrad(cv, gc, gs, gt, xc, xs, xt, gw, workspace, ws_bytes, (hipStream_t)stream);
 }
 
 int mxconv_im2col_cbf(const mxc_conv* p, int fmt, const void* xc, const uint8_t* xs, void* cc,
@@ -304,7 +311,7 @@ static int wgrad_call(const mxc_conv* p, int fmt, const void* gc, const uint8_t*
     if (!aligned16(gc) || !aligned16(gs) || !aligned16(xc) || !aligned16(xs) || !aligned16(gw) ||
         (need && !aligned16(workspace)))
         return MXC_ERR_ALIGN;
-    return launch_wgrad(cv, gc, gs, xc, xs, gw, workspace, (hipStream_t)stream, nullptr, nullptr, defer);
+    return launch_wgrad(cv, gc, gs, xc, xs, gw, workspace, (hipStream_t)stream, defer);
 }
 
 int mxconv_wgrad(const mxc_conv* p, int fmt, const void* gc, const uint8_t* gs, const void* xc,
@@ -461,7 +468,7 @@ int mxconv_wgrad_noalloc(const mxc_conv* p, int fmt, const void* gc, const uint8
         rc = scratch_for_current_device(&ws);
         if (rc) return rc;
     }
-    return launch_wgrad(cv, gc, gs, xc, xs, gw, ws, (hipStream_t)stream, nullptr, nullptr, false);
+    return launch_wgrad(cv, gc, gs, xc, xs, gw, ws, (hipStream_t)stream);
 }
 
 int mxconv_concat_cbf(int fmt, int n, int h, int w, int nparts, const mxc_part* parts, void* codes,

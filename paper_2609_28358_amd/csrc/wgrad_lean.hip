@@ -34,21 +34,22 @@ __global__ __launch_bounds__(WT) void wgrad_lean_kernel(WLArgs p) {
 
 // Splits of the lean weight-gradient kernel for this layer, or 0 when it does
 // not apply (batch block below 32).
-int wgrad_lean_splits(const Conv& cv) {
+int wgrad_lean_splits(const Conv& cv, bool nv) {
     if (cv.x.bn != 32) return 0;
     const long npix = (long)cv.x.ng * cv.ho * cv.wo;
     const long npairs = (npix + 1) / 2;
     const long ntiles = (long)cv.kh * cv.kw * ((cv.gy.ncb + 1) / 2) * ((cv.x.ncb + 1) / 2);
     if (npix > 0x3FFFFFFFL || ntiles > 0x7FFFFFL) return 0;
     // about two workgroups per CU, each wave with at least 4 pixel pairs; a
-    // layer on 32 x 32 tiles (one channel block on each side) keeps a quarter
-    // of the LDS per workgroup, so about five fit on a CU, each wave with at
-    // least 8 pairs
+    // layer with one channel block on each side takes 32 x 32 tiles, which
+    // keep a quarter of the LDS per workgroup, so about five fit on a CU, each
+    // wave with at least 8 pairs.  NVFP takes 64 x 64 tiles always; there the
+    // larger of the two counts measured fastest (16 channels at 160x160, batch
+    // 64, NVFP8: 281 us; 3 -> 16 at 640x640, batch 32, 566 with 142 splits, 588
+    // with 56).
+    const long two = std::min(512 / ntiles, npairs / 16), five = std::min(1280 / ntiles, npairs / 32);
     const bool nb1 = wgrad_single_block(cv);
-    long splits = (nb1 ? 1280 : 512) / ntiles;
-    const long cap = npairs / (4 * (nb1 ? 8 : 4));
-    if (splits > cap) splits = cap;
-    if (splits < 1) splits = 1;
+    const long splits = std::max(1L, !nb1 ? two : nv ? std::max(two, five) : five);
     return (int)splits;
 }
 

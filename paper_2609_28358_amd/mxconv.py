@@ -92,6 +92,7 @@ def lib():
         "mxconv_nvfp_quantize": (i32, [P, i32, i32, i32, i32, i32, i32, i32, i32, P, P, P, P, sz, P]),
         "mxconv_nvfp_fwd": (i32, [CP, i32, P, P, P, P, P, P, P, i32, P]),
         "mxconv_nvfp_dgrad": (i32, [CP, i32, P, P, P, P, P, P, P, i32, P]),
+        "mxconv_nvfp_wgrad_workspace_bytes": (sz, [CP, i32]),
         "mxconv_nvfp_wgrad": (i32, [CP, i32, P, P, P, P, P, P, P, P, sz, P]),
         "mxconv_im2col_cbf": (i32, [CP, i32, P, P, P, P, P]),
         "mxconv_fwd": (i32, [CP, i32, P, P, P, P, P, i32, P]),
@@ -212,6 +213,15 @@ def _wgrad_workspace_bytes(key, fmt):
 
 def wgrad_workspace_bytes(cv, fmt):
     return _wgrad_workspace_bytes(_conv_key(cv), fmt)
+
+
+@functools.lru_cache(maxsize=_CACHED, typed=True)
+def _nvfp_wgrad_workspace_bytes(key, fmt):
+    return lib().mxconv_nvfp_wgrad_workspace_bytes(ctypes.byref(_conv_of(key)), fmt)
+
+
+def nvfp_wgrad_workspace_bytes(cv, fmt):
+    return _nvfp_wgrad_workspace_bytes(_conv_key(cv), fmt)
 
 
 class MxTensor:
@@ -357,7 +367,7 @@ def nvfp_wgrad(cv, gy, x, out=None, workspace=None, stream=None):
     gw = out if out is not None else torch.empty((cv["cout"], cv["cin"], cv["kh"], cv["kw"]),
                                                  dtype=torch.float32, device=x.codes.device)
     fmt = pair(gy.fmt, x.fmt)
-    need = wgrad_workspace_bytes(cv, fmt)
+    need = nvfp_wgrad_workspace_bytes(cv, fmt)
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.codes.device)
     wsz = workspace.numel() * workspace.element_size() if workspace is not None else 0

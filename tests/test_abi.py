@@ -335,6 +335,34 @@ def test_nvfp_gemm_errors():
     assert w(r16, 1, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, 1 << 30, None) == -3
 
 
+@pytest.mark.parametrize("fmt", [mx.E4M3, mx.E2M1, mx.E2M3, mx.pair(mx.E2M1, mx.E3M2)])
+def test_nvfp_wgrad_workspace(fmt):
+    """The NVFP weight gradient's own split count: the one-tap 64 x 64 tile,
+    about 512 workgroups, at least 16 pixel pairs a split (one channel block
+    each side, FP8 or FP4: 1280 and 32, if that is more) -- whatever the layer's
+    MX form takes (both larger and smaller counts are here)."""
+    sides = set()
+    for cv in (synth.conv_dict(32, 64, 64, 56, 56, 3, 1, 1), synth.conv_dict(32, 128, 256, 28, 28, 3, 2, 1),
+               synth.conv_dict(128, 320, 320, 7, 7, 3, 1, 1), synth.conv_dict(32, 64, 256, 56, 56, 1, 1, 0),
+               synth.conv_dict(32, 3, 16, 640, 640, 3, 2, 1), synth.conv_dict(32, 256, 256, 14, 14, 3, 1, 1),
+               synth.conv_dict(32, 40, 70, 5, 4, 3, 1, 1), synth.conv_dict(128, 256, 256, 28, 28, 3, 1, 1)):
+        ho, wo = synth.out_hw(cv)
+        gb, xb, taps = -(-cv["cout"] // 32), -(-cv["cin"] // 32), cv["kh"] * cv["kw"]
+        tiles = taps * ((gb + 1) // 2) * ((xb + 1) // 2)
+        pairs = (cv["n"] // 32 * ho * wo + 1) // 2
+        splits = max(1, min(512 // tiles, pairs // 16))
+        if gb == xb == 1 and fmt in (mx.E4M3, mx.E2M1):
+            splits = max(splits, min(1280 // tiles, pairs // 32))
+        part = 4 * 32 * gb * taps * 32 * xb
+        assert mx.nvfp_wgrad_workspace_bytes(cv, fmt) == (splits * part if splits > 1 else 0)
+        sides.add((splits > max(1, mx.wgrad_workspace_bytes(cv, fmt) // part)) -
+                  (splits < max(1, mx.wgrad_workspace_bytes(cv, fmt) // part)))
+    assert {-1, 1} <= sides
+    for cv in (synth.conv_dict(16, 64, 64, 8, 8, 3, 1, 1),):
+        assert mx.nvfp_wgrad_workspace_bytes(cv, fmt) == 0
+    assert mx.nvfp_wgrad_workspace_bytes(synth.conv_dict(32, 64, 64, 56, 56, 3, 1, 1), mx.E3M2) == 0
+
+
 def test_wgrad_reduce_multi_errors():
     L = mx.lib()
     cv = mx.conv_struct(synth.conv_dict(32, 64, 64, 56, 56, 3, 1, 1))        # needs a split-K workspace

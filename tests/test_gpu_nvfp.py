@@ -186,6 +186,29 @@ def test_nvfp_gemms_full_size_layer(mx, method):
     assert max(errs) <= 1.0, max(errs)
 
 
+@pytest.mark.parametrize("method", list(NV_METHODS))
+@pytest.mark.parametrize("cv", [synth.conv_dict(32, 64, 64, 28, 28, 3, 1, 1), synth.conv_dict(64, 40, 24, 24, 24, 3, 1, 1),
+                                synth.conv_dict(64, 20, 33, 40, 24, 3, 2, 1), synth.conv_dict(32, 160, 96, 7, 7, 3, 1, 1)],
+                         ids=lambda cv: f"{cv['cin']}to{cv['cout']}_{cv['h']}x{cv['w']}")
+def test_nvfp_wgrad_in_either_workspace(mx, method, cv):
+    """The weight gradient in a workspace of exactly the bytes of its own query
+    and of the MX form's (fewer or more splits): right in both, nothing written
+    outside either."""
+    q, d = _nv_layer(mx, cv, 77, fmts=NV_METHODS[method])
+    ref = oracle.direct_wgrad(cv, d["gy"], d["x"])
+    mag = oracle.direct_wgrad(cv, np.abs(d["gy"]), np.abs(d["x"]))
+    fmt = mx.pair(q["gy"].fmt, q["x"].fmt)
+    for need in (mx.nvfp_wgrad_workspace_bytes(cv, fmt), mx.wgrad_workspace_bytes(cv, fmt)):
+        buf = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device=DEV)
+        gbuf = torch.full((ref.size + 64,), 7.0, device=DEV)
+        gw = gbuf[32:32 + ref.size].view(ref.shape)
+        mx.nvfp_wgrad(cv, q["gy"], q["x"], out=gw, workspace=buf[256:256 + need] if need else None)
+        torch.cuda.synchronize()
+        assert _nv_err(gw.cpu().numpy(), ref, mag) <= 1.0
+        assert bool((buf[:256] == 0xA5).all()) and bool((buf[256 + need:] == 0xA5).all())
+        assert bool((gbuf[:32] == 7.0).all()) and bool((gbuf[32 + ref.size:] == 7.0).all())
+
+
 def test_nvfp_gemm_refusals(mx):
     """Other element formats and layers outside the batch-block-32 kernels are refused."""
     cv = synth.conv_dict(32, 32, 32, 9, 9, 5, 1, 2)                 # kernel width 5
