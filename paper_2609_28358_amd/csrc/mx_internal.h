@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <algorithm>
+#include <type_traits>
 #include "../../include/mxconv.h"
 
 namespace mxc {

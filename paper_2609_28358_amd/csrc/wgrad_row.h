@@ -24,6 +24,21 @@ struct WRArgs {
     int nsplit;
 };
 
+// A fragment's registers (N of a row's bits / 4).  A vector, not an array: the
+// compiler joined the six words of an E2M3 fragment and the two behind them
+// into one 8-word read, which kept a slot of the ring in scratch memory (64
+// bytes a lane at column stride 2; MXFP6 32 -> 32 at 10x10, batch 32, stride
+// 2: 8.5 -> 7.4 us; 256 -> 256 at 28x28 27.9 -> 21.5).
+template <int N> struct WRFrag {
+    enum { n = N };
+    int d __attribute__((ext_vector_type(N)));
+};
+template <int N> struct WRCol {
+    enum { n = N };
+    int d[N];
+};
+template <typename T> constexpr int wr_words = std::remove_reference_t<T>::n;
+
 // Any offset past the tensor: a buffer load there returns zeros.
 constexpr uint32_t WR_OOB = 0x80000000u;
 __device__ __attribute__((aligned(16))) uint8_t g_zero_scale[16];
@@ -84,10 +99,10 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
 
     // fragments in the registers they need (4, 6 or 8), widened at the MFMA
     constexpr int FRA = fmt_bits(FA), FRB = fmt_bits(FB);
-    struct FragA { int d[FRA]; };
-    struct FragB { int d[FRB]; };
+    using FragA = WRFrag<FRA>;
+    using FragB = WRFrag<FRB>;
     auto wide = [](const auto& f) {
-        constexpr int N = sizeof(f.d) / 4;
+        constexpr int N = wr_words<decltype(f)>;
         v8i o;
 #pragma unroll
         for (int e = 0; e < 8; e++) o[e] = e < N ? f.d[e < N ? e : 0] : 0;
@@ -167,7 +182,7 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
     set_row();
 
     auto frag = [&](auto& o, auto rs, const uint32_t* v, uint32_t blk) {
-        constexpr int N = sizeof(o.d) / 4;
+        constexpr int N = wr_words<decltype(o)>;
         const v4i u = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, v[0], blk, 0));
 #pragma unroll
         for (int e = 0; e < 4; e++) o.d[e] = u[e];
@@ -229,7 +244,7 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
 
     // the window: per X column the fragments (FP8: decoded to bf16) and scales
     constexpr int WR = X8 ? 16 : FRB;
-    struct ColF { int d[WR]; };
+    using ColF = WRCol<WR>;
     struct Col {
         ColF f[NJ];
         int s[NJ];
