@@ -79,6 +79,22 @@ def test_against_oracle(mx, k, fg, fx):
             assert torch.equal(gw, gw2), f"layer {k}: backward's weight gradient differs"
 
 
+@pytest.mark.parametrize("fg,fx", [(0, 0), (1, 1), (2, 2), (1, 3)])
+@pytest.mark.parametrize("sw", [1, 2])
+def test_walks_of_every_length(mx, fg, fx, sw):
+    """Waves whose walk ends at each slot of the operand ring: one to nine
+    columns, row pairs complete and half empty."""
+    for w in range(1, 10):
+        for h in (2, 3):
+            cv = _cv(32, 24, 20, h, w, sh=1, sw=sw)
+            (qg, qx), (og, ox) = _operands(mx, cv, fg, fx, 500 + 10 * w + h)
+            gw = mx.wgrad(cv, qg, qx)
+            dims = tuple(gw.shape)
+            idx = np.stack(np.meshgrid(*[np.arange(d) for d in dims], indexing="ij"), -1).reshape(-1, 4)
+            r, s = oracle.wgrad_at(cv, fg if fg == fx else (fg, fx), og, ox, idx)
+            assert mxt.gemm_err(gw.cpu().numpy()[tuple(idx.T)], r, s) <= 1.0, (w, h)
+
+
 @pytest.mark.parametrize("fmt", [0, 1])
 @pytest.mark.parametrize("cv", [_cv(32, 24, 24, 6, 5), _cv(64, 70, 72, 33, 63)], ids=["32x32", "64x64"])
 def test_a_nan_reaches_its_taps_only(mx, fmt, cv):
