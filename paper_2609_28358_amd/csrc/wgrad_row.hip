@@ -41,6 +41,12 @@ void wr_launch(const WRArgs& a, int nb, int sw, dim3 gd, hipStream_t s) {
 //   FP8: always, the decoded window saves two of three decodes; 64 x 64 tiles
 //     where a wave walks at least 12 columns (256 -> 256 at 16 x 16, batch 128,
 //     89 -> 53 us), else 32 x 32 ones (64 -> 64 at 56 x 56, batch 32, 27 -> 19);
+//   64 x 64 tiles only where their grid takes nearly every CU, or a wave walks
+//     at least 64 columns: with 192 workgroups (512 channels on a side) 32 x 32
+//     ones are faster, and share a launch with the input gradient (MXFP8
+//     512 -> 256 at 14x14, batch 32: 37 -> 26 us alone, 59 -> 47 with it; MXFP4
+//     512 -> 512 at 10x10, batch 64: 32 -> 22 and 58 -> 40; MXFP8 512 -> 256 at
+//     40x40, batch 32, 100 columns a wave: 64 x 64 ones win, 118 against 130);
 //   FP4 / FP6 on more blocks: 64 x 64 tiles where a wave walks enough columns
 //     to cover the larger epilogue, column stride 1 (256 -> 256 as above 40 ->
 //     34; FP6 128 -> 128 at 40 x 40, batch 64, 33 -> 29); FP4 needs more of
@@ -67,8 +73,9 @@ bool wgrad_row_plan(const Conv& cv, WRPlan& q) {
     q.nb = 1;
     if (cv.gy.ncb > 1 || cv.x.ncb > 1) {
         const long cols = cv.gy.ncb > 1 && cv.x.ncb > 1 ? total / (4 * split(2)) : 0;
-        if (cv.fa == MXC_E4M3) q.nb = cols >= 12 ? 2 : 1;
-        else if (cv.sw == 1 && cols >= (fmt_bits(cv.fb) == 6 ? 16 : 24)) q.nb = 2;
+        const bool fills = split(2) * tiles(2) >= 224 || cols >= 64;
+        if (cv.fa == MXC_E4M3) q.nb = cols >= 12 && fills ? 2 : 1;
+        else if (cv.sw == 1 && cols >= (fmt_bits(cv.fb) == 6 ? 16 : 24)) q.nb = fills ? 2 : 1;
         else if (total > 128) return false;
     }
     const long nt = tiles(q.nb);

@@ -9,6 +9,7 @@ import re
 import pytest
 
 import oracle
+import wgrad_plan
 from paper_2609_28358_amd import mxconv as mx
 from paper_2609_28358_amd import synth
 
@@ -333,6 +334,24 @@ def test_nvfp_gemm_errors():
     assert w(big, 1, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, None, 0, None) == -6
     r16 = ctypes.byref(mx.conv_struct(synth.conv_dict(16, 64, 64, 8, 8, 3, 1, 1)))
     assert w(r16, 1, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, GOOD, 1 << 30, None) == -3
+
+
+@pytest.mark.parametrize("fg,fx", [(0, 0), (1, 1), (2, 2), (1, 3)])
+def test_wgrad_plan(fg, fx):
+    """The weight gradient's tile and split count, seen in its workspace."""
+    sides = set()
+    for n in (32, 64, 128):
+        for cin, cout in ((3, 16), (32, 32), (64, 64), (70, 100), (256, 128), (256, 512), (512, 512), (320, 320)):
+            for h, w in ((1, 1), (7, 7), (14, 14), (9, 23), (28, 28), (40, 40), (56, 56)):
+                for k, s in ((3, 1), (3, 2), (3, 3), (1, 1)):
+                    cv = synth.conv_dict(n, cin, cout, h, w, k, s, k // 2)
+                    assert mx.wgrad_workspace_bytes(cv, mx.pair(fg, fx)) == wgrad_plan.workspace_bytes(cv, fg, fx), cv
+                    sides.add((wgrad_plan.row_plan(cv, fg, fx) or (0,))[0])
+    assert sides == {0, 1, 2}
+    # wide layers with few columns: a grid of 64 x 64 tiles would leave a quarter of the GPU idle
+    for n, cin, cout, h, w in ((32, 512, 256, 14, 14), (64, 512, 512, 10, 10), (128, 512, 256, 7, 7)):
+        plan = wgrad_plan.row_plan(synth.conv_dict(n, cin, cout, h, w, 3, 1, 1), fg, fx)
+        assert plan is None or plan[0] == 1
 
 
 @pytest.mark.parametrize("fmt", [mx.E4M3, mx.E2M1, mx.E2M3, mx.pair(mx.E2M1, mx.E3M2)])
