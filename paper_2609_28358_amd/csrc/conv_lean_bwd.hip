@@ -12,43 +12,43 @@ struct WArgs {                // the weight gradient's arguments, by its tile
 };
 
 template <int F, int KW, int PW, bool DG2, int NB, int NRB = 2, bool KR = false>
-int bwd_launch(const LeanArgs& a, const WArgs& w, int nl, int grid, size_t lds, hipStream_t s) {
+int bwd_launch(const LeanArgs& a, const WArgs& w, int nl, bool dgf, int grid, size_t lds, hipStream_t s) {
     const BwdWArgs<KW, NB>* q;
     if constexpr (KW == 3 && NB == 1) q = &w.r;
     else                              q = &w.l;
     static std::atomic<uint64_t> devs{0};
     if (raise_lds(conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>, devs, lds)) return MXC_ERR_HIP;
-    hipLaunchKernelGGL((conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>), dim3(grid), dim3(LT), lds, s, a, *q, nl);
+    hipLaunchKernelGGL((conv_lean_bwd_kernel<F, KW, PW, DG2, NB, NRB, KR>), dim3(grid), dim3(LT), lds, s, a, *q, nl, dgf ? 1 : 0);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }
 
 template <int F, int NB>
-int bwd_launch_nb(const LeanArgs& a, const WArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
+int bwd_launch_nb(const LeanArgs& a, const WArgs& q, int nl, bool dgf, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
                   hipStream_t s) {
     if constexpr (F == MXC_E2M1) {
         if (pw == NARROW_PW) {
             if (kw == 3 && kr)
-                return dg2 ? bwd_launch<F, 3, NARROW_PW, true, NB, 1, true>(a, q, nl, grid, lds, s)
-                           : bwd_launch<F, 3, NARROW_PW, false, NB, 1, true>(a, q, nl, grid, lds, s);
-            if (dg2) return kw == 3 ? bwd_launch<F, 3, NARROW_PW, true, NB, 1>(a, q, nl, grid, lds, s)
-                                    : bwd_launch<F, 1, NARROW_PW, true, NB, 1>(a, q, nl, grid, lds, s);
-            return kw == 3 ? bwd_launch<F, 3, NARROW_PW, false, NB, 1>(a, q, nl, grid, lds, s)
-                           : bwd_launch<F, 1, NARROW_PW, false, NB, 1>(a, q, nl, grid, lds, s);
+                return dg2 ? bwd_launch<F, 3, NARROW_PW, true, NB, 1, true>(a, q, nl, dgf, grid, lds, s)
+                           : bwd_launch<F, 3, NARROW_PW, false, NB, 1, true>(a, q, nl, dgf, grid, lds, s);
+            if (dg2) return kw == 3 ? bwd_launch<F, 3, NARROW_PW, true, NB, 1>(a, q, nl, dgf, grid, lds, s)
+                                    : bwd_launch<F, 1, NARROW_PW, true, NB, 1>(a, q, nl, dgf, grid, lds, s);
+            return kw == 3 ? bwd_launch<F, 3, NARROW_PW, false, NB, 1>(a, q, nl, dgf, grid, lds, s)
+                           : bwd_launch<F, 1, NARROW_PW, false, NB, 1>(a, q, nl, dgf, grid, lds, s);
         }
     }
     if (dg2) {
-        if (kw == 3) return pw == 1 ? bwd_launch<F, 3, 1, true, NB>(a, q, nl, grid, lds, s) : bwd_launch<F, 3, 2, true, NB>(a, q, nl, grid, lds, s);
-        return pw == 1 ? bwd_launch<F, 1, 1, true, NB>(a, q, nl, grid, lds, s) : bwd_launch<F, 1, 2, true, NB>(a, q, nl, grid, lds, s);
+        if (kw == 3) return pw == 1 ? bwd_launch<F, 3, 1, true, NB>(a, q, nl, dgf, grid, lds, s) : bwd_launch<F, 3, 2, true, NB>(a, q, nl, dgf, grid, lds, s);
+        return pw == 1 ? bwd_launch<F, 1, 1, true, NB>(a, q, nl, dgf, grid, lds, s) : bwd_launch<F, 1, 2, true, NB>(a, q, nl, dgf, grid, lds, s);
     }
-    if (kw == 3) return pw == 1 ? bwd_launch<F, 3, 1, false, NB>(a, q, nl, grid, lds, s) : bwd_launch<F, 3, 2, false, NB>(a, q, nl, grid, lds, s);
-    return pw == 1 ? bwd_launch<F, 1, 1, false, NB>(a, q, nl, grid, lds, s) : bwd_launch<F, 1, 2, false, NB>(a, q, nl, grid, lds, s);
+    if (kw == 3) return pw == 1 ? bwd_launch<F, 3, 1, false, NB>(a, q, nl, dgf, grid, lds, s) : bwd_launch<F, 3, 2, false, NB>(a, q, nl, dgf, grid, lds, s);
+    return pw == 1 ? bwd_launch<F, 1, 1, false, NB>(a, q, nl, dgf, grid, lds, s) : bwd_launch<F, 1, 2, false, NB>(a, q, nl, dgf, grid, lds, s);
 }
 
 template <int F>
-int bwd_launch_f(const LeanArgs& a, const WArgs& q, int nl, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
+int bwd_launch_f(const LeanArgs& a, const WArgs& q, int nl, bool dgf, int grid, size_t lds, bool dg2, int kw, int pw, bool kr,
                  bool nb1, hipStream_t s) {
-    return nb1 ? bwd_launch_nb<F, 1>(a, q, nl, grid, lds, dg2, kw, pw, kr, s)
-               : bwd_launch_nb<F, 2>(a, q, nl, grid, lds, dg2, kw, pw, kr, s);
+    return nb1 ? bwd_launch_nb<F, 1>(a, q, nl, dgf, grid, lds, dg2, kw, pw, kr, s)
+               : bwd_launch_nb<F, 2>(a, q, nl, dgf, grid, lds, dg2, kw, pw, kr, s);
 }
 
 }  // namespace
@@ -92,7 +92,16 @@ int launch_lean_bwd(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     size_t lds = lean_lds(a, used);
     if (lds < (size_t)red) lds = (size_t)red;
     const int grid = (int)(nl + wg);
-    return f == MXC_E4M3 ? bwd_launch_f<MXC_E4M3>(a, q, (int)nl, grid, lds, P.dg2, dcv.kw, P.pw, P.krow, nb1, s)
-                         : bwd_launch_f<MXC_E2M1>(a, q, (int)nl, grid, lds, P.dg2, dcv.kw, P.pw, P.krow, nb1, s);
+    // The longer workgroups are dispatched first: an input-gradient tile runs
+    // its taps times G_Y's channel blocks, a wave of the kernel-row tile its
+    // columns.  Between the two orders: 512 -> 512 at 7x7, batch 32, stride 2,
+    // MXFP8, 36 steps against 2: 30 us weight gradient first, 21.5 input gradient
+    // first; 512 -> 256 at 20x20, batch 64, MXFP4, 72 against 100: 49 and 61.  The
+    // line lies where they cross, at 2.5 steps a column.  One-tap tiles, whose
+    // workgroups are about as long, go first.
+    const long steps = (long)dcv.kh * dcv.kw * dcv.gy.ncb;                  // stride 2: a quarter, on average
+    const bool dgf = row && 2 * steps >= 5L * q.r.spw * (P.dg2 ? 4 : 1);
+    return f == MXC_E4M3 ? bwd_launch_f<MXC_E4M3>(a, q, (int)nl, dgf, grid, lds, P.dg2, dcv.kw, P.pw, P.krow, nb1, s)
+                         : bwd_launch_f<MXC_E2M1>(a, q, (int)nl, dgf, grid, lds, P.dg2, dcv.kw, P.pw, P.krow, nb1, s);
 }
 }  // namespace mxc

@@ -1147,9 +1147,9 @@ __global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void co
 
 // The input gradient of a layer (stride 1 with KW taps per row, or, with
 // DG2, the four stride-2 phases of kernel width KW) and its weight gradient
-// in one launch: the last nl workgroups take input-gradient tiles, the ones
-// before them weight-gradient tiles (dispatched first: measured faster than
-// the other order).  Both only read the quantized G_Y (with W, resp. X), so
+// in one launch: nl workgroups take input-gradient tiles, the others
+// weight-gradient tiles; dg_first: in that order, else the other way round
+// (launch_lean_bwd picks).  Both only read the quantized G_Y (with W, resp. X), so
 // neither waits for the other, and the tail of one fills the CUs the other
 // leaves idle.  Both counts are multiples of 8, so each part keeps its own
 // kernel's XCD mapping.  Format F for every operand.
@@ -1157,13 +1157,14 @@ __global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void co
 // tap for 1-wide kernels, of a kernel row (wgrad_row.h) for 3-wide ones.
 template <int KW, int NB> using BwdWArgs = std::conditional_t<KW == 3 && NB == 1, WRArgs, WLArgs>;
 template <int F, int KW, int PW, bool DG2, int NB, int NRB = 2, bool KR = false>
-__global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void conv_lean_bwd_kernel(LeanArgs p, BwdWArgs<KW, NB> q, int nl) {
+__global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void conv_lean_bwd_kernel(LeanArgs p, BwdWArgs<KW, NB> q, int nl, int dg_first) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int b = blockIdx.x;
     const int nw = (int)gridDim.x - nl;
-    if (b >= nw) {
-        if constexpr (DG2) lean_dg2_body<F, F, KW, 1, PW, false, NRB, KR, false>(p, b - nw, nl);
-        else               lean_body<F, F, true, KW, 1, 1, PW, false, NRB, KR, false>(p, b - nw, nl);
+    const int b = (int)blockIdx.x - (dg_first ? nl : 0);      // weight-gradient workgroup, if in [0, nw)
+    if (b < 0 || b >= nw) {
+        const int d = dg_first ? (int)blockIdx.x : b - nw;
+        if constexpr (DG2) lean_dg2_body<F, F, KW, 1, PW, false, NRB, KR, false>(p, d, nl);
+        else               lean_body<F, F, true, KW, 1, 1, PW, false, NRB, KR, false>(p, d, nl);
     } else {
         float (*const red)[32 * NB * 32 * NB] = (float (*)[32 * NB * 32 * NB])smem;
         if constexpr (KW == 3 && NB == 1) wgrad_row_tile<F, F, 1, DG2 ? 2 : 1, 4>(q, b, nw, red);
