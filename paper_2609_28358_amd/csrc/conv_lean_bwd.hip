@@ -94,11 +94,12 @@ int launch_lean_bwd(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     const int grid = (int)(nl + wg);
     // The longer workgroups are dispatched first: an input-gradient tile runs
     // its taps times G_Y's channel blocks, a wave of the kernel-row tile its
-    // columns.  Between the two orders: 512 -> 512 at 7x7, batch 32, stride 2,
-    // MXFP8, 36 steps against 2: 30 us weight gradient first, 21.5 input gradient
-    // first; 512 -> 256 at 20x20, batch 64, MXFP4, 72 against 100: 49 and 61.  The
-    // line lies where they cross, at 2.5 steps a column.  One-tap tiles, whose
-    // workgroups are about as long, go first.
+    // columns.  Between the two orders (us, weight gradient first, then last):
+    // MXFP8 512 -> 512 at 7x7, batch 32, stride 2, 36 steps against 2: 30 and 21.5;
+    // 256 -> 512 at 14x14, stride 2, 36 against 7: 31.7 and 23.6; MXFP4 512 -> 256
+    // at 20x20, batch 64, 72 against 100: 49 and 61.  The line lies where they
+    // cross, at 2.5 steps a column.  One-tap tiles, whose workgroups are about
+    // as long, go first.
     const long steps = (long)dcv.kh * dcv.kw * dcv.gy.ncb;                  // stride 2: a quarter, on average
     const bool dgf = row && 2 * steps >= 5L * q.r.spw * (P.dg2 ? 4 : 1);
     return f == MXC_E4M3 ? bwd_launch_f<MXC_E4M3>(a, q, (int)nl, dgf, grid, lds, P.dg2, dcv.kw, P.pw, P.krow, nb1, s)

@@ -19,16 +19,20 @@ __global__ __launch_bounds__(WRT, NB == 2 ? 1 : 2) void wgrad_row_kernel(WRArgs 
     wgrad_row_tile<FA, FB, NB, S, wr_depth<FA, FB, NB>()>(p, blockIdx.x, gridDim.x, red);
 }
 
+// The column strides each tile side is built for: FP4 / FP6 take 64 x 64 tiles
+// at column stride 1 only.
 template <int FA, int FB>
-void wr_launch(const WRArgs& a, int nb, int sw, dim3 gd, hipStream_t s) {
-    if (nb == 2) {
-        // FP4 / FP6 take 64 x 64 tiles at column stride 1 only
-        if (FA != MXC_E4M3 || sw == 1) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 1>), gd, dim3(WRT), 0, s, a);
-        else if constexpr (FA == MXC_E4M3)
-            hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 2>), gd, dim3(WRT), 0, s, a);
+int wr_launch(const WRArgs& a, int nb, int sw, dim3 gd, hipStream_t s) {
+    if (nb == 1 && sw == 1)      hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 1>), gd, dim3(WRT), 0, s, a);
+    else if (nb == 1 && sw == 2) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 2>), gd, dim3(WRT), 0, s, a);
+    else if (nb == 2 && sw == 1) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 1>), gd, dim3(WRT), 0, s, a);
+    else if constexpr (FA == MXC_E4M3) {
+        if (nb != 2 || sw != 2) return MXC_ERR_ARG;
+        hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 2, 2>), gd, dim3(WRT), 0, s, a);
+    } else {
+        return MXC_ERR_ARG;
     }
-    else if (sw == 2) hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 2>), gd, dim3(WRT), 0, s, a);
-    else              hipLaunchKernelGGL((wgrad_row_kernel<FA, FB, 1, 1>), gd, dim3(WRT), 0, s, a);
+    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }
 
 }  // namespace
@@ -96,12 +100,11 @@ int launch_wgrad_row(const Conv& cv, const void* gc, const uint8_t* gs, const vo
     if (!wgrad_row_plan(cv, q)) return MXC_ERR_SHAPE;
     WRArgs a;
     const dim3 gd((unsigned)wgrad_row_fill(cv, q, gc, gs, xc, xs, dst, a));
-    if (cv.fa == MXC_E4M3 && cv.fb == MXC_E4M3)      wr_launch<MXC_E4M3, MXC_E4M3>(a, q.nb, cv.sw, gd, s);
-    else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E2M1) wr_launch<MXC_E2M1, MXC_E2M1>(a, q.nb, cv.sw, gd, s);
-    else if (cv.fa == MXC_E2M3 && cv.fb == MXC_E2M3) wr_launch<MXC_E2M3, MXC_E2M3>(a, q.nb, cv.sw, gd, s);
-    else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E3M2) wr_launch<MXC_E2M1, MXC_E3M2>(a, q.nb, cv.sw, gd, s);
-    else return MXC_ERR_ARG;
-    return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
+    if (cv.fa == MXC_E4M3 && cv.fb == MXC_E4M3) return wr_launch<MXC_E4M3, MXC_E4M3>(a, q.nb, cv.sw, gd, s);
+    if (cv.fa == MXC_E2M1 && cv.fb == MXC_E2M1) return wr_launch<MXC_E2M1, MXC_E2M1>(a, q.nb, cv.sw, gd, s);
+    if (cv.fa == MXC_E2M3 && cv.fb == MXC_E2M3) return wr_launch<MXC_E2M3, MXC_E2M3>(a, q.nb, cv.sw, gd, s);
+    if (cv.fa == MXC_E2M1 && cv.fb == MXC_E3M2) return wr_launch<MXC_E2M1, MXC_E3M2>(a, q.nb, cv.sw, gd, s);
+    return MXC_ERR_ARG;
 }
 
 }  // namespace mxc

@@ -10,6 +10,7 @@ import torch
 
 import mx_tolerance as mxt
 import oracle
+import wgrad_plan
 from paper_2609_28358_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -42,7 +43,11 @@ LAYERS = [
     _cv(32, 8, 8, 40, 57),                           # many splits, some waves past the end
     _cv(64, 70, 72, 33, 63),                         # 64 x 64 tiles, the third block of each side alone
     _cv(64, 70, 72, 65, 64, sh=2, sw=2),
+    _cv(32, 70, 72, 67, 64),                         # 64 x 64 tiles, the last row pair half empty
+    _cv(32, 70, 72, 133, 129, sh=2, sw=2),
 ]
+# 64 x 64 tiles: these layers, the strided ones in FP8 only
+WIDE = {8: False, 9: True, 10: False, 11: True}
 
 
 def _operands(mx, cv, fg, fx, seed, x=None, gy=None):
@@ -77,6 +82,19 @@ def test_against_oracle(mx, k, fg, fx):
             gw2 = mx.backward(cv, qw, qg, qx)[1]
             torch.cuda.synchronize()
             assert torch.equal(gw, gw2), f"layer {k}: backward's weight gradient differs"
+
+
+@pytest.mark.parametrize("fg,fx", [(0, 0), (1, 1), (2, 2), (1, 3)])
+def test_layers_reach_their_tiles(mx, fg, fx):
+    for k, cv in enumerate(LAYERS):
+        plan = wgrad_plan.row_plan(cv, fg, fx)
+        if k in WIDE:
+            assert (plan is not None and plan[0] == 2) == (fg == 0 or not WIDE[k]), (k, plan)
+        else:
+            assert plan is not None and plan[0] == 1, (k, plan)
+        assert mx.wgrad_workspace_bytes(cv, mx.pair(fg, fx)) == wgrad_plan.workspace_bytes(cv, fg, fx)
+    odd = [k for k in WIDE if (LAYERS[k]["n"] // 32 * synth.out_hw(LAYERS[k])[0]) % 2]
+    assert {WIDE[k] for k in odd} == {False, True}
 
 
 @pytest.mark.parametrize("fg,fx", [(0, 0), (1, 1), (2, 2), (1, 3)])
