@@ -28,26 +28,37 @@ constexpr int QT = 256;            // threads per workgroup
 
 __device__ __forceinline__ int swz(int u) { return ((u >> 5) ^ (u >> 1)) & 7; }
 
-// Four consecutive source elements as floats (bf16 widened exactly).
+// One source element (VEC 1) or four consecutive ones as loaded: floats, a bf16
+// value's bits in a float's upper half, or four bf16; and as floats.
+template <int DTYPE, int VEC> struct Raw { typedef float4 t; };
+template <> struct Raw<MXC_BF16, 4> { typedef uint2 t; };
 template <int DTYPE, int VEC>
-__device__ __forceinline__ float4 load4(const void* src, size_t i) {
-    if (VEC == 4) {
-        if (DTYPE == MXC_F32) return __ldg((const float4*)((const float*)src + i));
-        const uint2 b = __ldg((const uint2*)((const unsigned short*)src + i));
-        return make_float4(__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u),
-                           __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u));
-    }
-    float v;
-    if (DTYPE == MXC_F32) v = __ldg((const float*)src + i);
-    else v = __uint_as_float((uint32_t)__ldg((const unsigned short*)src + i) << 16);
-    return make_float4(v, 0.0f, 0.0f, 0.0f);
+__device__ __forceinline__ typename Raw<DTYPE, VEC>::t load_raw(const void* src, size_t i) {
+    if constexpr (VEC == 4 && DTYPE == MXC_F32) return __ldg((const float4*)((const float*)src + i));
+    else if constexpr (VEC == 4)                return __ldg((const uint2*)((const unsigned short*)src + i));
+    else if constexpr (DTYPE == MXC_F32)        return make_float4(__ldg((const float*)src + i), 0.0f, 0.0f, 0.0f);
+    else return make_float4(__uint_as_float((uint32_t)__ldg((const unsigned short*)src + i) << 16), 0.0f, 0.0f, 0.0f);
 }
+__device__ __forceinline__ float4 widen(float4 v) { return v; }
+__device__ __forceinline__ float4 widen(uint2 b) {
+    return make_float4(__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u), __uint_as_float(b.y << 16),
+                       __uint_as_float(b.y & 0xFFFF0000u));
+}
+__device__ __forceinline__ void clear(float4& v) { v = make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
+__device__ __forceinline__ void clear(uint2& v) { v = make_uint2(0u, 0u); }
 
 // VEC = 4: every thread moves 8 runs of 4 consecutive elements along the
 // source's contiguous dimension (16-byte loads); VEC = 1: 32 single elements.
-// All loads of a slab are issued before any is consumed (addresses of
-// out-of-range elements are clamped to the tensor's first element and the
-// value replaced by zero), so each thread has its whole slab share in flight.
+// All loads of a slab are issued before any is consumed, so each thread has
+// its whole slab share in flight.  A slab inside the tensor loads without
+// conditions; at its edges only the lanes with an element load (measured: 3
+// channels at 640 x 640, batch 32, to MXFP4: NHWC fp32 340 us; with the others
+// reading the tensor's first element 789, as the lanes' lines then left the L1
+// between their four uses).  bf16 quads are widened after the last load -- in
+// between, each would wait for its own (NHWC bf16, 64 channels at 80 x 80, batch
+// 64: 26.8 -> 20.6 us).  Single bf16 elements keep one form, lanes without an
+// element reading the first one: the compiler overlaps those (the image above
+// 335 us, 792 with conditions, 396 with both forms).
 __device__ __forceinline__ float comp(const float4& v, int t) {
     return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w;
 }
@@ -137,38 +148,53 @@ __global__ __launch_bounds__(QT) void quantize_kernel(const void* __restrict__ s
     const int p0 = pb * tt;
 
     // ---- 1. load (all loads first), then store into the slab in code order
-    float4 v[NL];
+    typename Raw<DTYPE, VEC>::t raw[NL];
     int ci0[NL];
+    constexpr bool SPLIT = VEC == 4 || DTYPE == MXC_F32;   // separate code for slabs inside the tensor
+    auto load_all = [&](auto whole) {
 #pragma unroll
-    for (int r = 0; r < NL; r++) {
-        const int e = (tid + QT * r) * VEC;
-        int pl, cl, j;
-        if (LAYOUT == MXC_NCHW) {
-            pl = e & (tt - 1); const int r1 = e >> ltt; cl = r1 & 31; j = r1 >> 5;
-        } else if (LAYOUT == MXC_NHWC) {
-            cl = e & 31; const int r1 = e >> 5; pl = r1 & (tt - 1); j = r1 >> ltt;
-        } else {
-            j = e & (bn - 1); const int r1 = e >> lbn; cl = r1 & 31; pl = r1 >> 5;
+        for (int r = 0; r < NL; r++) {
+            const int e = (tid + QT * r) * VEC;
+            int pl, cl, j;
+            if (LAYOUT == MXC_NCHW) {
+                pl = e & (tt - 1); const int r1 = e >> ltt; cl = r1 & 31; j = r1 >> 5;
+            } else if (LAYOUT == MXC_NHWC) {
+                cl = e & 31; const int r1 = e >> 5; pl = r1 & (tt - 1); j = r1 >> ltt;
+            } else {
+                j = e & (bn - 1); const int r1 = e >> lbn; cl = r1 & 31; pl = r1 >> 5;
+            }
+            const int pix = p0 + pl, c = cb * 32 + cl, n = ng * bn + j;
+            size_t gi;
+            if (LAYOUT == MXC_NCHW)      gi = ((size_t)n * g.c + c) * hw + pix;
+            else if (LAYOUT == MXC_NHWC) gi = ((size_t)n * hw + pix) * g.c + c;
+            else                         gi = (((size_t)ng * hw + pix) * g.c + c) * bn + j;
+            ci0[r] = ((pl * 32 + cl) << lbn) + j;          // canonical index of the first element
+            if constexpr (decltype(whole)::value) {
+                raw[r] = load_raw<DTYPE, VEC>(src, gi);
+            } else {
+                const bool ok = pix < hw && c < g.c && n < g.n;
+                if constexpr (SPLIT) {
+                    clear(raw[r]);
+                    if (ok) raw[r] = load_raw<DTYPE, VEC>(src, gi);
+                } else {
+                    raw[r] = load_raw<DTYPE, VEC>(src, ok ? gi : 0);
+                    if (!ok) clear(raw[r]);
+                }
+            }
         }
-        const int pix = p0 + pl, c = cb * 32 + cl, n = ng * bn + j;
-        const bool ok = pix < hw && c < g.c && n < g.n;
-        size_t gi;
-        if (LAYOUT == MXC_NCHW)      gi = ((size_t)n * g.c + c) * hw + pix;
-        else if (LAYOUT == MXC_NHWC) gi = ((size_t)n * hw + pix) * g.c + c;
-        else                         gi = (((size_t)ng * hw + pix) * g.c + c) * bn + j;
-        v[r] = load4<DTYPE, VEC>(src, ok ? gi : 0);
-        if (!ok) v[r] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        ci0[r] = ((pl * 32 + cl) << lbn) + j;          // canonical index of the first element
-    }
+    };
+    if (SPLIT && p0 + tt <= hw && cb * 32 + 32 <= g.c) load_all(std::bool_constant<SPLIT>{});
+    else                                               load_all(std::false_type{});
 #pragma unroll
     for (int r = 0; r < NL; r++) {
+        const float4 v = widen(raw[r]);
         if (LAYOUT == MXC_CBF && VEC == 4) {
             // four consecutive samples: one 16-byte chunk of the slab
             const int u = ci0[r] >> 5, k = ci0[r] & 31;
-            *(float4*)&slab[u * 32 + (((k >> 2) ^ swz(u)) << 2)] = v[r];
+            *(float4*)&slab[u * 32 + (((k >> 2) ^ swz(u)) << 2)] = v;
             continue;
         }
-        const float x4[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+        const float x4[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int q = 0; q < VEC; q++) {
             // the q-th element steps along the contiguous dimension

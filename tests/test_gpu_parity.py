@@ -59,6 +59,26 @@ def test_quantize_nchw_f32(mx, fmt, shape):
 NARROW_SHAPES = [(32, 3, 17, 19), (64, 3, 40, 40), (32, 1, 8, 8), (96, 4, 5, 13), (64, 2, 1, 130), (32, 3, 64, 64)]
 
 
+@pytest.mark.parametrize("fmt", [0, 1, 2])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc", "cbf"])
+@pytest.mark.parametrize("shape", [(32, 70, 5, 7), (64, 36, 4, 5), (16, 68, 9, 4), (8, 33, 6, 6), (4, 64, 11, 12)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_quantize_slabs_inside_and_at_edges(mx, fmt, layout, shape, bf16):
+    """Whole and partial channel blocks and pixel runs in one tensor, single
+    elements and runs of four."""
+    n, c, h, w = shape
+    t = synth.normal(shape, 1.0, 61 + c) * torch.exp(synth.normal(shape, 2.0, 6))
+    if bf16:
+        t = t.to(torch.bfloat16).float()
+    src = {"nchw": t, "nhwc": t.permute(0, 2, 3, 1).contiguous(), "cbf": synth.nchw_to_cbf(t, min(n, 32))}[layout]
+    lay = {"nchw": mx.NCHW, "nhwc": mx.NHWC, "cbf": mx.CBF}[layout]
+    g = mx.quantize((src.to(torch.bfloat16) if bf16 else src).to(DEV), mx.ACT, fmt, layout=lay, shape=shape)
+    codes, scales = oracle.quantize(t.numpy(), oracle.NCHW, mx.ACT, fmt, *shape)
+    assert np.array_equal(g.scales.cpu().numpy(), scales)
+    assert np.array_equal(g.codes.cpu().numpy()[:len(codes)], codes)       # FP6 buffers end in slack
+
+
 @pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("shape", NARROW_SHAPES, ids=lambda s: "x".join(map(str, s)))
