@@ -137,9 +137,8 @@ __global__ __launch_bounds__(QT) void quantize_kernel(const void* __restrict__ s
     // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs, so give
     // each XCD a contiguous range of slabs (neighbouring pixel blocks share
     // cache lines in NCHW).
-    const int nwg = gridDim.x;
-    const int per_xcd = (nwg + 7) / 8;
-    const int slab_id = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    const uint32_t per_xcd = gridDim.x * gridDim.y / 8, wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const int slab_id = (int)(wg % 8 * per_xcd + wg / 8);      // below 2^31
     if (slab_id >= nslabs) return;
     const int pb = slab_id % pixblocks;
     const int rest = slab_id / pixblocks;
@@ -758,13 +757,16 @@ int launch_q(const void* src, const Geom& g, void* codes, uint8_t* scales, hipSt
     // (one slab per workgroup: two in turn, so that neighbouring pixel blocks
     // of an NCHW source share cache lines, measured slower -- 32 channels at
     // 80 x 80, batch 16, bf16: 9.0 against 6.7 us)
-    if (nslabs > 0x7FFFFFF0L) return MXC_ERR_SHAPE;
-    const int grid = ((int)nslabs + 7) / 8 * 8;     // whole rounds over the 8 XCDs
+    if (nslabs > 0x7F000000L) return MXC_ERR_SHAPE;     // workgroups of whole rows: below 2^31
+    // whole rounds over the 8 XCDs; a launch holds less than 2^32 threads along
+    // x, so past 2^23 slabs the grid has rows of that many
+    const long wgs = (nslabs + 7) / 8 * 8, row = 1L << 23;
+    const dim3 grid((unsigned)std::min(wgs, row), (unsigned)((wgs + row - 1) / row));
     if (vec4)
-        hipLaunchKernelGGL((quantize_kernel<LAYOUT, DTYPE, FMT, 4, SR>), dim3(grid), dim3(QT), 0, s, src, g,
+        hipLaunchKernelGGL((quantize_kernel<LAYOUT, DTYPE, FMT, 4, SR>), grid, dim3(QT), 0, s, src, g,
                            (uint8_t*)codes, scales, (int)nslabs, pixblocks, k0, k1);
     else
-        hipLaunchKernelGGL((quantize_kernel<LAYOUT, DTYPE, FMT, 1, SR>), dim3(grid), dim3(QT), 0, s, src, g,
+        hipLaunchKernelGGL((quantize_kernel<LAYOUT, DTYPE, FMT, 1, SR>), grid, dim3(QT), 0, s, src, g,
                            (uint8_t*)codes, scales, (int)nslabs, pixblocks, k0, k1);
     return hipGetLastError() == hipSuccess ? MXC_OK : MXC_ERR_HIP;
 }

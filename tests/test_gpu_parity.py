@@ -79,6 +79,19 @@ def test_quantize_slabs_inside_and_at_edges(mx, fmt, layout, shape, bf16):
     assert np.array_equal(g.codes.cpu().numpy()[:len(codes)], codes)       # FP6 buffers end in slack
 
 
+def test_quantize_past_one_row_of_workgroups(mx):
+    """2^24 + 3 channel blocks at one pixel, one workgroup each: more than a
+    launch takes along one dimension.  The same codes as in two halves."""
+    half = 1 << 28
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    src = torch.empty(2 * half + 70, dtype=torch.bfloat16, device=DEV).normal_(generator=gen)
+    g = mx.quantize(src, mx.ACT, 0, mx.NCHW, (1, src.numel(), 1, 1))
+    for a, b in ((0, half), (half, src.numel())):
+        q = mx.quantize(src[a:b], mx.ACT, 0, mx.NCHW, (1, b - a, 1, 1))
+        assert torch.equal(g.codes[a:a + q.codes.numel()], q.codes)
+        assert torch.equal(g.scales[a // 32:a // 32 + q.scales.numel()], q.scales)
+
+
 @pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
 @pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
 @pytest.mark.parametrize("shape", NARROW_SHAPES, ids=lambda s: "x".join(map(str, s)))
