@@ -105,8 +105,9 @@ __device__ __forceinline__ uint32_t wave_block() {
     return blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 }
 
-// NT: 1 or 2 terms none of which is a 2x2 patch sum, all loads issued before
-// the first value is used; 0: any terms.  Bound by HBM: measured with one
+// NT: that many terms, none of which is a 2x2 patch sum, all loads issued before
+// the first value is used; 0: any terms (one load of a row at a time: three
+// fp32 terms and SiLU', 64 channels at 80x80, batch 64, FP8 47 us, 36 with NT 3).  Bound by HBM: measured with one
 // term and SiLU', 32 channels at 160 x 160, batch 64, bf16 60.8 -> 47.6 us
 // (236 MB: the copy rate), 16 channels 38.5 -> 26.2; fp32, 256 channels at
 // 16 x 16, batch 128, 15.4 -> 12.2 us.
@@ -121,28 +122,35 @@ __global__ __launch_bounds__(256) void quantize_sum_kernel(SumArgs a, uint8_t* _
     const int j = 4 * (lane & 7);
     float4 v[4];
     if constexpr (NT > 0) {
+        // rows of eight channels that hold any (uniform: a block of few channels
+        // does no work for the others)
+        const int nq = min(4, (a.c - cb * 32 + 7) / 8);
         float4 u[NT][4], zz[4];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int ch = cb * 32 + 8 * q + (lane >> 3);
             const bool ok = ch < a.c;
+            zz[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int t = 0; t < NT; t++) u[t][q] = zz[q];
+            if (q >= nq) continue;
 #pragma unroll
             for (int t = 0; t < NT; t++)
-                u[t][q] = ok ? load_nt((const float*)a.src[t] + ((size_t)pix * a.c_src[t] + a.c_off[t] + ch) * 32 + j)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
-            zz[q] = ok && a.fn != MXC_FN_NONE ? load_nt((const float*)a.z + ((size_t)pix * a.c + ch) * 32 + j)
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
+                if (ok) u[t][q] = load_nt((const float*)a.src[t] + ((size_t)pix * a.c_src[t] + a.c_off[t] + ch) * 32 + j);
+            if (ok && a.fn != MXC_FN_NONE) zz[q] = load_nt((const float*)a.z + ((size_t)pix * a.c + ch) * 32 + j);
         }
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             v[q] = u[0][q];
-            if constexpr (NT == 2) { v[q].x += u[1][q].x; v[q].y += u[1][q].y; v[q].z += u[1][q].z; v[q].w += u[1][q].w; }
+#pragma unroll
+            for (int t = 1; t < NT; t++) { v[q].x += u[t][q].x; v[q].y += u[t][q].y; v[q].z += u[t][q].z; v[q].w += u[t][q].w; }
         }
         if (a.fn != MXC_FN_NONE)
             with_fn(a.fn, [&](auto t) {
                 constexpr int F = decltype(t)::fn;
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
+                    if (q >= nq) continue;
                     v[q].x *= fn_grad_c<F>(zz[q].x);
                     v[q].y *= fn_grad_c<F>(zz[q].y);
                     v[q].z *= fn_grad_c<F>(zz[q].z);
@@ -395,6 +403,10 @@ void launch_sum(const SumArgs& a, int nt, bool bf16, dim3 gd, uint8_t* codes, ui
                 hipStream_t s) {
     if (nt == 1)      launch_sum_nt<FMT, 1, SR>(a, bf16, gd, codes, scales, nblocks, s);
     else if (nt == 2) launch_sum_nt<FMT, 2, SR>(a, bf16, gd, codes, scales, nblocks, s);
+    // (bf16 sums of three and four take the general form: half the loads, and
+    // none of them slower for it)
+    else if (nt == 3 && !bf16) hipLaunchKernelGGL((quantize_sum_kernel<FMT, 3, SR>), gd, dim3(256), 0, s, a, codes, scales, nblocks);
+    else if (nt == 4 && !bf16) hipLaunchKernelGGL((quantize_sum_kernel<FMT, 4, SR>), gd, dim3(256), 0, s, a, codes, scales, nblocks);
     else              launch_sum_nt<FMT, 0, SR>(a, bf16, gd, codes, scales, nblocks, s);
 }
 
@@ -446,7 +458,7 @@ int launch_quantize_sum(const Geom& dst, int fmt, const mxc_term* terms, int nte
     if (nblocks <= 0) return MXC_OK;
     if (nblocks > 0x7FFFFFFFLL) return MXC_ERR_SHAPE;
     const dim3 gd((unsigned)((nblocks + 3) / 4));
-    bool plain = nterms <= 2;
+    bool plain = true;
     for (int t = 0; t < nterms; t++) plain &= !terms[t].down;
     const int nt = plain ? nterms : 0;
     uint8_t* const cd = (uint8_t*)codes;

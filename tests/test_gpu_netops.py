@@ -91,6 +91,8 @@ SUM_CASES = [
     (32, 64, 3, 3, [(64, 0, 0), (128, 64, 1), (64, 0, 0), (192, 0, 0)], 2),
     (32, 40, 7, 9, [(40, 0, 0), (80, 40, 0)], 0),
     (32, 48, 4, 6, [(96, 16, 0), (48, 0, 1)], 1),                # ReLU
+    (32, 3, 5, 7, [(3, 0, 0), (8, 5, 0), (3, 0, 0), (4, 1, 0)], 2),   # four plain terms, few channels
+    (64, 41, 4, 3, [(41, 0, 0), (64, 8, 0), (41, 0, 0)], 0),
 ]
 
 
@@ -136,6 +138,31 @@ def test_quantize_sum_errors(mx):
         mx.quantize_sum(ok, (32, 32, 4, 4), 2)                       # FP6 not offered
     with pytest.raises(mx.MxconvError, match="code -1"):
         mx.quantize_sum(ok, (32, 32, 4, 4), 0, fn=mx.FN_SILU)        # SiLU' needs z
+
+
+@pytest.mark.parametrize("sr", [None, 5], ids=["rne", "sr"])
+@pytest.mark.parametrize("bf", [False, True], ids=["f32", "bf16"])
+@pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
+@pytest.mark.parametrize("c,nt,fn", [(1, 1, 2), (8, 2, 2), (9, 3, 1), (40, 3, 2), (72, 2, 0)])
+def test_quantize_sum_plain_as_any(mx, c, nt, fn, fmt, bf, sr):
+    """Plain terms, any number of them and rows that hold no channel, against the
+    form that takes any terms (reached by a 2x2 patch sum of zeros)."""
+    dt = torch.bfloat16 if bf else torch.float32
+    cbf = lambda ch, std, seed: synth.nchw_to_cbf(synth.normal((64, ch, 5, 3), std, seed), 32).to(dt).to(DEV)
+    terms = [(cbf(c + 8 * k, 1e-3, 50 + k), c + 8 * k, 8 * k, 0) for k in range(nt)]
+    patch = [(torch.zeros((2, 10, 6, c, 32), dtype=dt, device=DEV), c, 0, 1)]
+    z = cbf(c, 2.0, 60)
+    got = []
+    for ts in (terms, terms + patch):
+        vals = torch.full((2, 5, 3, c, 32), float("nan"), device=DEV)
+        out = mx.MxTensor.empty(mx.ACT, fmt, (64, c, 5, 3), DEV)
+        _garbage(out.codes), _garbage(out.scales)
+        mx.quantize_sum(ts, (64, c, 5, 3), fmt, fn=fn | (mx.FN_BF16 if bf else 0), z=z if fn else None, out=out,
+                        vals=vals, sr_seed=sr)
+        got.append((out.codes, out.scales, vals))
+    torch.cuda.synchronize()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("sr", [None, 5], ids=["rne", "sr"])
