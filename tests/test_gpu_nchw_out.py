@@ -20,6 +20,11 @@ LAYERS = [
     (synth.conv_dict(64, 24, 17, 34, 37, 3, 2), 1),
     (synth.conv_dict(32, 64, 48, 20, 26, 3, 2), 0),
     (synth.conv_dict(32, 64, 40, 11, 10, 3, 1), 2),
+    (synth.conv_dict(64, 3, 16, 34, 37, 3, 2), 1),         # few rows: 3 (16 wide tiles), 1, 5, 33 and 8
+    (synth.conv_dict(64, 1, 5, 30, 33, 1, 1), 1),
+    (synth.conv_dict(32, 5, 3, 9, 10, 3, 1), 0),
+    (synth.conv_dict(32, 33, 1, 17, 19, 3, 2), 0),
+    (synth.conv_dict(32, 8, 35, 20, 21, 3, 1), 2),
 ]
 
 
