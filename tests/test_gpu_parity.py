@@ -283,6 +283,19 @@ def test_nonfinite_block_propagates(mx):
 
 # ------------------------------------------------------------------ full-size layers
 @pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
+@pytest.mark.parametrize("n,h,w,k,s", [(2, 61, 1, 3, 1), (2, 1, 60, 3, 1), (4, 45, 2, 3, 2), (8, 23, 19, 5, 1), (2, 30, 41, 3, 3)])
+def test_wgrad_small_batches(mx, fmt, n, h, w, k, s):
+    """Batches below 32 with more K ranges than rows: ranges that start and end
+    inside an output row, rows of one pixel, one row."""
+    cv = synth.conv_dict(n, 40, 24, h, w, k, s, k // 2)
+    x, _, gy = synth.layer_inputs(cv, 800 + h, kind="unit")
+    q = [mx.quantize(t.to(DEV), mx.ACT, fmt) for t in (gy, x)]
+    o = [oracle.quantize(t.numpy(), oracle.NCHW, oracle.ACT, fmt, *t.shape) for t in (gy, x)]
+    r, sa = oracle.wgrad(cv, fmt, *o)
+    assert _err(mx.wgrad(cv, *q).cpu().numpy(), r, sa) <= 1.0
+
+
+@pytest.mark.parametrize("fmt", [0, 1], ids=["e4m3", "e2m1"])
 @pytest.mark.parametrize("li", range(len(synth.SWEEP_LAYERS)), ids=[n for n, _ in synth.SWEEP_LAYERS])
 def test_sweep_layer_full_size(mx, fmt, li):
     """The benchmark's layers at full size, in the launch configuration the
