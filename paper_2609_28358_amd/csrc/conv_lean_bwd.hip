@@ -68,7 +68,7 @@ int launch_lean_bwd(const Conv& dcv, const void* wc, const uint8_t* ws, const vo
     WArgs q;
     WRPlan wr;
     const bool row = wgrad_row_plan(wcv, wr);
-    if (row && wr.nb != 1) return 1;                     // one wave per SIMD: a launch of its own
+    if (row && (wr.nb != 1 || wr.launches > 1)) return 1;   // one wave per SIMD, or 2 GiB of codes: launches of its own
     const bool nb1 = row || (wgrad_single_block(wcv) && wcv.kw == 1);
     if (!row && !nb1 && wgrad_single_block(wcv)) return 1;
     const long wg = row ? wgrad_row_fill(wcv, wr, gc, gs, xc, xs, wdst, q.r)

@@ -136,11 +136,14 @@ int launch_wgrad_lean(const Conv& cv, const void* gc, const uint8_t* gs, const v
                       float* dst, int splits, hipStream_t s, const float* nv_tg = nullptr,
                       const float* nv_tx = nullptr);
 // the kernel-row weight gradient of 3-wide MX layers (wgrad_row.hip): the
-// tile side in 32-row blocks, tiles, row pairs and splits (false: another
-// kernel serves the layer); its splits, or 0; and the launch (dst: partial
-// tiles with more than one split, else G_W)
+// launches it takes and the batch groups of each (more than one for tensors
+// past a buffer descriptor's 2 GiB), the tile side in 32-row blocks, tiles, row
+// pairs and splits per launch, splits in all (false: another kernel serves the
+// layer); its splits in all, or 0; and the launch (dst: partial tiles with more
+// than one split in all, else G_W)
 struct WRPlan {
-    int nb, ntiles, nrp, splits;
+    int launches, groups;
+    int nb, ntiles, nrp, per, splits;
 };
 bool wgrad_row_plan(const Conv& cv, WRPlan& q);
 int wgrad_row_splits(const Conv& cv);

@@ -389,8 +389,9 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
     }
 }
 
-// The tile arguments for one layer (dst: G_W with one split, else the partial
-// tiles); returns the workgroup count, a multiple of 8.
+// The tile arguments for one launch of a layer (cv: its batch groups; dst: G_W
+// with one split in all, else this launch's partial tiles); returns the
+// workgroup count, a multiple of 8.
 inline long wgrad_row_fill(const Conv& cv, const WRPlan& q, const void* gc, const uint8_t* gs, const void* xc,
                            const uint8_t* xs, float* dst, WRArgs& a) {
     a.gc = (const uint8_t*)gc; a.gs = gs; a.xc = (const uint8_t*)xc; a.xs = xs;
@@ -403,14 +404,14 @@ inline long wgrad_row_fill(const Conv& cv, const WRPlan& q, const void* gc, cons
     a.gbytes = (uint32_t)((long)cv.gy.ng * cv.ho * cv.wo * cv.gy.cp * 4 * fmt_bits(cv.fa));
     a.xbytes = (uint32_t)((long)cv.x.ng * cv.h * cv.w * cv.x.cp * 4 * fmt_bits(cv.fb));
     a.nrows = cv.x.ng * cv.ho;
-    a.nrp = q.nrp;
+    a.nrp = (a.nrows + 1) / 2;
     a.cot = (cv.gy.ncb + q.nb - 1) / q.nb;
     a.cit = (cv.x.ncb + q.nb - 1) / q.nb;
     a.ntiles = q.ntiles;
-    const long total = (long)q.nrp * cv.wo, waves = 4L * q.splits;
+    const long total = (long)a.nrp * cv.wo, waves = 4L * q.per;
     a.spw = (int)((total + waves - 1) / waves);
-    a.nsplit = q.splits;
-    return ((long)q.ntiles * q.splits + 7) / 8 * 8;
+    a.nsplit = q.per;
+    return ((long)q.ntiles * q.per + 7) / 8 * 8;
 }
 
 }  // namespace

@@ -61,18 +61,26 @@ int wr_launch(const WRArgs& a, int nb, int sw, dim3 gd, hipStream_t s) {
 //     any to walk.
 bool wgrad_row_plan(const Conv& cv, WRPlan& q) {
     if (cv.x.bn != 32 || cv.kw != 3 || (cv.sw != 1 && cv.sw != 2)) return false;
-    const long gb = (long)cv.gy.ng * cv.ho * cv.wo * cv.gy.cp * 4 * fmt_bits(cv.fa);
-    const long xb = (long)cv.x.ng * cv.h * cv.w * cv.x.cp * 4 * fmt_bits(cv.fb);
-    if (gb >= 0x7FFFFF00L || xb >= 0x7FFFFF00L) return false;   // 32-bit buffer offsets
-    q.nrp = (cv.x.ng * cv.ho + 1) / 2;
-    const long total = (long)q.nrp * cv.wo;                           // columns of all row pairs
+    // 32-bit buffer offsets: codes below 2 GiB per launch.  A larger layer of one
+    // channel block on each side takes its batch groups in several launches (3 ->
+    // 16 at 640x640, batch 192, MXFP8: 807 us in one-tap tiles, 369 so); the others
+    // have one-tap tiles for that size.
+    const long gb = (long)cv.ho * cv.wo * cv.gy.cp * 4 * fmt_bits(cv.fa);    // of one group
+    const long xb = (long)cv.h * cv.w * cv.x.cp * 4 * fmt_bits(cv.fb);
+    const long fit = 0x7FFFFF00L / std::max(gb, xb);
+    if (fit == 0) return false;
+    q.launches = (int)((cv.x.ng + fit - 1) / fit);
+    q.groups = (cv.x.ng + q.launches - 1) / q.launches;
+    if (q.launches > 1 && (cv.gy.ncb > 1 || cv.x.ncb > 1)) return false;
+    q.nrp = (q.groups * cv.ho + 1) / 2;
+    const long total = (long)q.nrp * cv.wo;                           // columns of a launch's row pairs
     const long part = (long)cv.gy.cp * cv.kh * 3 * cv.x.cp * 4;       // bytes of one partial result
     auto tiles = [&](int n) { return (long)cv.kh * ((cv.gy.ncb + n - 1) / n) * ((cv.x.ncb + n - 1) / n); };
     // one workgroup per CU on 64 x 64 tiles (a wave per SIMD by their
     // registers), two on 32 x 32 ones; a wave walks at least 6 columns; the
     // partial results stay within 16 MiB
     auto split = [&](int n) {
-        return std::max(1L, std::min({(n == 2 ? 256 : 512) / tiles(n), total / (4 * 6), (16L << 20) / part}));
+        return std::max(1L, std::min({(n == 2 ? 256 : 512) / tiles(n), total / (4 * 6), (16L << 20) / part / q.launches}));
     };
     q.nb = 1;
     if (cv.gy.ncb > 1 || cv.x.ncb > 1) {
@@ -85,7 +93,9 @@ bool wgrad_row_plan(const Conv& cv, WRPlan& q) {
     const long nt = tiles(q.nb);
     if (nt > 0x7FFFFFL) return false;
     q.ntiles = (int)nt;
-    q.splits = (int)split(q.nb);
+    q.per = (int)split(q.nb);
+    if ((long)q.per * q.launches > std::max(1L, (16L << 20) / part)) return false;
+    q.splits = q.per * q.launches;
     return true;
 }
 
@@ -98,13 +108,24 @@ int launch_wgrad_row(const Conv& cv, const void* gc, const uint8_t* gs, const vo
                      hipStream_t s) {
     WRPlan q;
     if (!wgrad_row_plan(cv, q)) return MXC_ERR_SHAPE;
-    WRArgs a;
-    const dim3 gd((unsigned)wgrad_row_fill(cv, q, gc, gs, xc, xs, dst, a));
-    if (cv.fa == MXC_E4M3 && cv.fb == MXC_E4M3) return wr_launch<MXC_E4M3, MXC_E4M3>(a, q.nb, cv.sw, gd, s);
-    if (cv.fa == MXC_E2M1 && cv.fb == MXC_E2M1) return wr_launch<MXC_E2M1, MXC_E2M1>(a, q.nb, cv.sw, gd, s);
-    if (cv.fa == MXC_E2M3 && cv.fb == MXC_E2M3) return wr_launch<MXC_E2M3, MXC_E2M3>(a, q.nb, cv.sw, gd, s);
-    if (cv.fa == MXC_E2M1 && cv.fb == MXC_E3M2) return wr_launch<MXC_E2M1, MXC_E3M2>(a, q.nb, cv.sw, gd, s);
-    return MXC_ERR_ARG;
+    Conv part = cv;                                        // the batch groups of one launch
+    for (int g0 = 0; g0 < cv.x.ng; g0 += q.groups) {
+        const int l = g0 / q.groups;
+        const size_t gpix = (size_t)g0 * cv.ho * cv.wo, xpix = (size_t)g0 * cv.h * cv.w;
+        part.x.ng = part.gy.ng = std::min(q.groups, cv.x.ng - g0);
+        WRArgs a;
+        const dim3 gd((unsigned)wgrad_row_fill(part, q, (const uint8_t*)gc + gpix * cv.gy.cp * 4 * fmt_bits(cv.fa),
+                                               gs + gpix * cv.gy.ncb, (const uint8_t*)xc + xpix * cv.x.cp * 4 * fmt_bits(cv.fb),
+                                               xs + xpix * cv.x.ncb,
+                                               dst + (size_t)l * q.per * cv.gy.cp * cv.kh * 3 * cv.x.cp, a));
+        int rc = MXC_ERR_ARG;
+        if (cv.fa == MXC_E4M3 && cv.fb == MXC_E4M3)      rc = wr_launch<MXC_E4M3, MXC_E4M3>(a, q.nb, cv.sw, gd, s);
+        else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E2M1) rc = wr_launch<MXC_E2M1, MXC_E2M1>(a, q.nb, cv.sw, gd, s);
+        else if (cv.fa == MXC_E2M3 && cv.fb == MXC_E2M3) rc = wr_launch<MXC_E2M3, MXC_E2M3>(a, q.nb, cv.sw, gd, s);
+        else if (cv.fa == MXC_E2M1 && cv.fb == MXC_E3M2) rc = wr_launch<MXC_E2M1, MXC_E3M2>(a, q.nb, cv.sw, gd, s);
+        if (rc) return rc;
+    }
+    return MXC_OK;
 }
 
 }  // namespace mxc

@@ -125,3 +125,31 @@ def test_a_nan_reaches_its_taps_only(mx, fmt, cv):
     assert torch.isnan(gw[:, :32, :, :2]).all()      # the whole 32-channel block shares the NaN scale
     assert not torch.isnan(gw[:, :, :, 2]).any()
     assert not torch.isnan(gw[:, 32:]).any()
+
+
+@pytest.mark.parametrize("fmt,n,cin,cout,h,sw", [(0, 192, 3, 16, 640, 2), (1, 736, 24, 8, 430, 1)])
+def test_tensors_past_two_gib(mx, fmt, n, cin, cout, h, sw):
+    """Codes of 2 GiB and more, in launches of some batch groups each: against
+    the sum, in 64 bits, of the groups' own gradients."""
+    cv = _cv(n, cin, cout, h, h, sh=sw, sw=sw)
+    assert wgrad_plan.row_plan(cv, fmt, fmt) is not None
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    ho, wo = synth.out_hw(cv)
+
+    def tensor(c, hh, ww):
+        q = mx.MxTensor.empty(mx.ACT, fmt, (n, c, hh, ww), DEV)
+        q.codes.random_(0, 0x7F, generator=gen).bitwise_and_(0x7F if fmt == 0 else 0x77)   # positive, no NaN
+        q.scales.random_(118, 124, generator=gen)
+        return q
+    qx, qg = tensor(cin, h, h), tensor(cout, ho, wo)
+    assert max(qx.codes.numel(), qg.codes.numel()) >= 1 << 31
+    gw = mx.wgrad(cv, qg, qx)
+    ng = n // 32
+    one = dict(cv, n=32)
+    ref = torch.zeros(gw.shape, dtype=torch.float64, device=DEV)
+    for g in range(ng):
+        part = [mx.MxTensor(t.codes[g * (t.codes.numel() // ng):(g + 1) * (t.codes.numel() // ng)].clone(),
+                            t.scales[g * (t.scales.numel() // ng):(g + 1) * (t.scales.numel() // ng)].clone(),
+                            mx.ACT, fmt, (32,) + t.shape[1:]) for t in (qg, qx)]
+        ref += mx.wgrad(one, *part).double()
+    assert bool(((gw.double() - ref).abs() <= 1e-5 * ref).all())   # positive products: their sum is the bound's scale

@@ -19,20 +19,26 @@ def one_tap_splits(cv, fg, fx):
 
 
 def row_plan(cv, fg, fx):
-    """(tile side in 32-row blocks, splits) of the kernel-row tile, or None:
-    another kernel serves the layer."""
+    """(tile side in 32-row blocks, splits in all) of the kernel-row tile, or
+    None: another kernel serves the layer."""
     if cv["n"] % 32 or cv["kw"] != 3 or cv["sw"] not in (1, 2):
         return None
     ho, wo = _out(cv)
     ng, gb, xb = cv["n"] // 32, -(-cv["cout"] // 32), -(-cv["cin"] // 32)
-    total = (ng * ho + 1) // 2 * wo
+    fit = 0x7FFFFF00 // max(ho * wo * gb * 128 * BITS[fg], cv["h"] * cv["w"] * xb * 128 * BITS[fx])
+    if fit == 0:
+        return None
+    launches = -(-ng // fit)                 # each below 2 GiB of codes
+    if launches > 1 and (gb > 1 or xb > 1):
+        return None
+    total = (-(-ng // launches) * ho + 1) // 2 * wo
     part = 32 * gb * cv["kh"] * 3 * 32 * xb * 4
 
     def tiles(k):
         return cv["kh"] * -(-gb // k) * -(-xb // k)
 
     def split(k):
-        return max(1, min((256 if k == 2 else 512) // tiles(k), total // 24, (16 << 20) // part))
+        return max(1, min((256 if k == 2 else 512) // tiles(k), total // 24, (16 << 20) // part // launches))
 
     nb = 1
     if gb > 1 or xb > 1:
@@ -44,7 +50,7 @@ def row_plan(cv, fg, fx):
             nb = 2 if fills else 1
         elif total > 128:
             return None
-    return nb, split(nb)
+    return (nb, split(nb) * launches) if split(nb) * launches <= max(1, (16 << 20) // part) else None
 
 
 def workspace_bytes(cv, fg, fx):
