@@ -69,6 +69,10 @@ bool wgrad_row_plan(const Conv& cv, WRPlan& q) {
     const long xb = (long)cv.h * cv.w * cv.x.cp * 4 * fmt_bits(cv.fb);
     const long fit = 0x7FFFFF00L / std::max(gb, xb);
     if (fit == 0) return false;
+    // a row that does not exist is walked from WR_OOB on; its last column must
+    // lie below 2^32 too (rows of many channels under wide padding reach past it)
+    const long step = std::max((long)cv.gy.cp * 4 * fmt_bits(cv.fa), (long)cv.sw * cv.x.cp * 4 * fmt_bits(cv.fb));
+    if ((cv.wo + 3) * step >= 0x7FFFF000L) return false;
     q.launches = (int)((cv.x.ng + fit - 1) / fit);
     q.groups = (cv.x.ng + q.launches - 1) / q.launches;
     if (q.launches > 1 && (cv.gy.ncb > 1 || cv.x.ncb > 1)) return false;

@@ -350,6 +350,14 @@ def test_wgrad_plan(fg, fx):
                     assert nb < 2 or s == 1 or fg == 0        # the 64 x 64 tiles that are built
                     sides.add(nb)
     assert sides == {0, 1, 2}
+    # one row of 2048 input channels under padding far wider than the input: the
+    # walk along it passes 32-bit offsets, so another kernel takes it
+    wide = dict(n=32, cin=2048, cout=32, h=1, w=9, kh=1, kw=3, sh=1, sw=1, ph=0, pw=40000)
+    assert wgrad_plan.row_plan(wide, fg, fx) is None
+    assert mx.wgrad_workspace_bytes(wide, mx.pair(fg, fx)) == wgrad_plan.workspace_bytes(wide, fg, fx)
+    narrow = dict(wide, pw=40)
+    assert wgrad_plan.row_plan(narrow, fg, fx) is not None or fg != 0
+    assert mx.wgrad_workspace_bytes(narrow, mx.pair(fg, fx)) == wgrad_plan.workspace_bytes(narrow, fg, fx)
     # wide layers with few columns: a grid of 64 x 64 tiles would leave a quarter of the GPU idle
     for n, cin, cout, h, w in ((32, 512, 256, 14, 14), (64, 512, 512, 10, 10), (128, 512, 256, 7, 7)):
         plan = wgrad_plan.row_plan(synth.conv_dict(n, cin, cout, h, w, 3, 1, 1), fg, fx)

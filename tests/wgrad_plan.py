@@ -26,7 +26,8 @@ def row_plan(cv, fg, fx):
     ho, wo = _out(cv)
     ng, gb, xb = cv["n"] // 32, -(-cv["cout"] // 32), -(-cv["cin"] // 32)
     fit = 0x7FFFFF00 // max(ho * wo * gb * 128 * BITS[fg], cv["h"] * cv["w"] * xb * 128 * BITS[fx])
-    if fit == 0:
+    # the padded width of a row fits the offsets, too
+    if fit == 0 or (wo + 3) * max(gb * 128 * BITS[fg], cv["sw"] * xb * 128 * BITS[fx]) >= 0x7FFFF000:
         return None
     launches = -(-ng // fit)                 # each below 2 GiB of codes
     if launches > 1 and (gb > 1 or xb > 1):
