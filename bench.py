@@ -20,8 +20,10 @@ a GPU spin, so the events bracket kernels, not host launch latency);
 `traffic` comes from the committed FETCH_SIZE / WRITE_SIZE counter summary of
 the same step (profiles/), while the sources still hash to it.
 
-Extra keys: `yolo_step` (every call's in-step time and roofline fraction,
-time by kind, per-layer algorithmic bytes against the naive comparator);
+The printed line is short (its headline is read from the end of a log); with
+`--detail FILE` the file holds all of it: `yolo_step` (every call's in-step
+time and roofline fraction, time by kind, per-layer algorithmic bytes against
+the naive comparator);
 `latent_replay_step` (the quantized-latent-replay back stack at batch 128,
 MXFP4, measured the same way); `layer_sweep` (the three-layer sweep at batch
 32 in MXFP8 and MXFP4 with steady-state per-op times, the measured naive
@@ -30,9 +32,9 @@ legs, the NVFP GEMMs of every element-format combination); `cpu_baseline`
 (the fp64 oracle on a bounded sample of the headline
 workload, on the host).
 
-    python bench.py [--steps K] [--warmup W] [--no-cpu-baseline] [--no-sweep] [--no-qlr]
+    python bench.py [--steps K] [--warmup W] [--no-cpu-baseline] [--no-sweep] [--no-qlr] [--detail FILE]
     python bench.py --pmc-pass {yolo,qlr,sweep}        (under rocprofv3 --pmc)
-    python bench.py --summarize-trace DIR LOG | --summarize-pmc FDIR WDIR FLOG WLOG
+    python bench.py --summarize-trace DIR DETAIL_FILE | --summarize-pmc FDIR WDIR FLOG WLOG
     python bench.py --summarize-sq LOG DIR [DIR ...]    (SQ counters of the MFMA-heavy calls)
 """
 import argparse
@@ -979,8 +981,8 @@ def _short(name):
 
 
 def summarize_trace(rdir, log):
-    """Markdown summary of `rocprofv3 --kernel-trace --stats` over a default
-    run of this script: the YOLO-shaped step's kernels in step order (median
+    """Markdown summary of `rocprofv3 --kernel-trace --stats` over a run of this
+    script with --detail (log: that file): the YOLO-shaped step's kernels in step order (median
     duration over every occurrence of the step in the run, beside the
     in-step times the bench line measured with HIP events), the roofline
     kernel's average, and every kernel of the run."""
@@ -1005,7 +1007,7 @@ def summarize_trace(rdir, log):
     L = ["# Kernel trace: YOLOv8n-shaped fwd+bwd step, batch 64, MXFP4\n"]
     L.append("Command (repository root on an MI355X machine, <out> an output directory; summary written by bench.py --summarize-trace):\n")
     L.append("    cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats --output-format csv "
-             "-d <out>/ktrace -o run -- python3 <repo>/bench.py > <out>/ktrace.log\n")
+             "-d <out>/ktrace -o run -- python3 <repo>/bench.py --detail <out>/detail.json > <out>/ktrace.log\n")
     rl = bench["roofline"]
     L.append(f"Bench line of the same run: value {bench['value']} TFLOP/s, {bench['ms_per_step']} ms per step; "
              f"roofline call `{rl['kernel']}` {rl['ms'] * 1000:.1f} us in the step (bound {rl['bound']}, achieved "
@@ -1172,12 +1174,25 @@ def summarize_sq(log, *dirs):
     return "\n".join(L) + "\n"
 
 
+def brief(out):
+    """The line to print, short enough for a log's tail: the headline, and of
+    the legs their totals and longest calls.  Everything is in --detail's file."""
+    line = {k: v for k, v in out.items() if k != "layer_sweep"}
+    for leg in ("yolo_step", "latent_replay_step"):
+        if leg in line:
+            line[leg] = {k: v for k, v in line[leg].items() if k not in ("all_calls", "bytes_vs_naive", "roofline")}
+            line[leg]["top_calls"] = line[leg]["top_calls"][:5]
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--detail", default=None, metavar="FILE",
+                    help="also write every call, layer and side leg, as one JSON line")
     ap.add_argument("--no-sweep", action="store_true", help="skip the layer-sweep leg")
     ap.add_argument("--no-qlr", action="store_true", help="skip the latent-replay leg")
     ap.add_argument("--no-naive", action="store_true", help="skip the naive comparator leg")
@@ -1189,7 +1204,7 @@ def main():
                     help="counter-collection pass over one workload's step (see pmc_pass)")
     ap.add_argument("--layers", default="all", help="layer sweep: comma list of layer indices (profiling aid)")
     ap.add_argument("--fmts", default="0,1", help="layer sweep: formats")
-    ap.add_argument("--summarize-trace", nargs=2, metavar=("ROCPROF_DIR", "BENCH_LOG"),
+    ap.add_argument("--summarize-trace", nargs=2, metavar=("ROCPROF_DIR", "DETAIL_FILE"),
                     help="write the kernel-trace summary of a rocprofv3 run of this script to stdout")
     ap.add_argument("--summarize-sq", nargs="+", metavar="LOG_THEN_DIRS",
                     help="SQ-counter summary: the --pmc-pass log, then the rocprofv3 output directories")
@@ -1283,7 +1298,10 @@ def main():
         out["layer_sweep"] = sweep
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline_net(net)
-    print(json.dumps(out))
+    if args.detail:
+        with open(args.detail, "w") as f:
+            print(json.dumps(out), file=f)
+    print(json.dumps(brief(out)))
 
 
 if __name__ == "__main__":
