@@ -393,9 +393,13 @@ int mxconv_wgrad_reduce_multi(int count, const mxc_wjob* jobs, void* stream);
 /* Both gradients of one layer (Eqs. (2) and (3), Sec. II-C) from one call:
  * mxconv_dgrad's result in gx and mxconv_wgrad's (deferred = 0) or
  * mxconv_wgrad_deferred's (deferred = 1) in gw / workspace, bit for bit.
- * Both products read the same quantized G_Y; with batch block 32, kernel
+ * Both products read the same quantized G_Y.  With batch block 32, kernel
  * width 1 or 3, stride 1 or 2 and format MXFP8 or MXFP4 they run as one
- * launch, otherwise as the two calls one after the other.
+ * launch, except where the weight gradient takes a launch of its own: 3-wide
+ * layers large enough for its 64 x 64 kernel-row tiles (all of a SIMD's
+ * registers), tensors past 2 GiB, and a few narrow shapes that the grouped
+ * kernel is not built for.  Those, and every other layer, run as the two
+ * calls one after the other.
  *   fmt              passed to both products as their fmt (so the pair
  *                    (W, G_Y) and the pair (G_Y, X) have the same formats).
  *                    A mixed MXC_PAIR(a, b) with a != b is refused (ARG):

@@ -737,7 +737,7 @@ struct RJob {
 struct RMulti {
     int wg0[MXC_WREDUCE_MAX];
     RJob j[MXC_WREDUCE_MAX];
-    int count, nwg;
+    int nwg;
 };
 
 __global__ __launch_bounds__(256) void wgrad_reduce_multi(RMulti m) {
@@ -1566,7 +1566,6 @@ int launch_wgrad_reduce_multi(int count, const WReduceJob* jobs, hipStream_t s) 
         nwg += wgs;
     }
     if (nq == 0) return MXC_OK;
-    m.count = nq;
     m.nwg = (int)nwg;
     for (int i = nq; i < MXC_WREDUCE_MAX; i++) { m.wg0[i] = m.nwg; m.j[i] = m.j[nq - 1]; }
     hipLaunchKernelGGL(wgrad_reduce_multi, dim3((unsigned)nwg), dim3(256), 0, s, m);

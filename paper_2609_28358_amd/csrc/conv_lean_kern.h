@@ -1122,7 +1122,9 @@ __device__ __forceinline__ void lean_body(const LeanArgs& p, int bid, int nblk) 
 // latency of each stage and epilogue exposed.  Held to 256 they fit in 120
 // to 170 with no spills, so two or three workgroups share a CU (measured on
 // the network step: the forward kernels about 18% faster, the narrow
-// stride-2 input gradient 21%).
+// stride-2 input gradient 21%).  The exception: the MXFP8 grouped-backward
+// kernels whose weight gradient takes 64 x 64 tiles need all 256 and spill
+// four (20 bytes of scratch).
 template <int FW, int FX, bool DG, int KW, int S, int WGM, int PW, bool NV = false, int NRB = 2, bool KR = false>
 __global__ __launch_bounds__(LT) __attribute__((amdgpu_waves_per_eu(2))) void conv_lean_kernel(LeanArgs p) {
     lean_body<FW, FX, DG, KW, S, WGM, PW, NV, NRB, KR>(p, blockIdx.x, gridDim.x);

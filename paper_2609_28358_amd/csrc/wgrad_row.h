@@ -87,7 +87,9 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
     const uint32_t gblk[2] = {(uint32_t)cob * TBA, (uint32_t)min(cob + 1, p.gy_ncb - 1) * TBA};
     const uint32_t xblk[2] = {(uint32_t)cib * TBB, (uint32_t)min(cib + 1, p.x_ncb - 1) * TBB};
     // a lane whose channel row is padding reads row 0 of its block, a line
-    // the real rows fetch anyway (its products are not written either)
+    // the real rows fetch anyway.  Its products are not zero: where the layer
+    // is split they reach the padding entries of the partial sums, which the
+    // reduction must not read (it stops at cout and drops ci >= cin).
     const uint32_t la = (cob * 32 + r < p.cout ? r * RBA : 0) + (X8 ? 16 * hf : 0);
     const uint32_t lb = (cib * 32 + r < p.cin ? r * RBB : 0) + (X8 ? 16 * hf : 0);
     const uint32_t gpix = (uint32_t)p.gy_ncb * TBA, xpix = (uint32_t)p.x_ncb * TBB;

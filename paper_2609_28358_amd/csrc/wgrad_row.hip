@@ -9,7 +9,7 @@ namespace mxc {
 namespace {
 
 // Operand slots in flight (steps): as many as the registers beside the
-// accumulators hold without spilling; deeper rings measured no faster.
+// accumulators hold without scratch memory; deeper rings measured no faster.
 template <int FA, int FB, int NB>
 constexpr int wr_depth() { return NB == 2 && (FA == MXC_E4M3 || fmt_bits(FB) == 6) ? 3 : 4; }
 
