@@ -436,8 +436,10 @@ def sweep_leg(args):
         return pmc_pass(calls, "sweep")
 
     # Per-op GPU time: each op alone, behind a GPU spin so that the event pair
-    # brackets the kernel(s) and not the host's launch latency.
+    # brackets the kernel(s) and not the host's launch latency; one call first,
+    # so that no rep holds the loading of a kernel (1 ms for a kernel's first).
     def op_time(j, op, reps=5):
+        run(j, op)
         marks = []
         for _ in range(reps):
             torch.cuda._sleep(SPIN_CYCLES)
