@@ -348,18 +348,25 @@ __device__ __forceinline__ void wgrad_row_tile(const WRArgs& p, int bid, int nbl
 
 #pragma unroll
     for (int b = 0; b < D - 1; b++) { load(sl[b]); next_row(); }
-    for (int k = 0; k < nstream; k += D) {       // loads, and steps, past the end bring and add nothing
+    // Whole rings without a test in them, then the steps that are left: a walk
+    // ends with its last step (short ones lost up to D - 1 empty steps: MXFP4
+    // 192 -> 384 at 10x10, batch 64, stride 2, 9.9 -> 9.0 us), and one block holds
+    // a whole ring, so its steps overlap (against a test before each step: MXFP8
+    // 320 -> 320 at 7x7, batch 128, 26.4 -> 24.5 us; MXFP4 3 -> 16 at 640x640, batch
+    // 32, 37.2 -> 35.7).  Loads past the end bring nothing.
+    auto slot = [&](int b) {
+        step(sl[b], sl[(b + D - 1) % D], cs >= cmin);
+        next_row();
+        if (++cs == p.wo + PR) { cs = 0; cmin = PR; }
+    };
+    int ks = 0;
+    for (; ks + D <= nstream; ks += D) {
 #pragma unroll
-        for (int b = 0; b < D; b++) {
-            // a short walk (a few columns a wave) ends with its last step, not
-            // with the ring's last slot: MXFP8 32 -> 32 at 10x10, batch 32, stride
-            // 2, 8.6 -> 7.9 us.  The straight-line form keeps its one block.
-            if ((X8 || NI * NJ < 4) && k + b >= nstream) break;
-            step(sl[b], sl[(b + D - 1) % D], k + b < nstream && cs >= cmin);
-            next_row();
-            if (++cs == p.wo + PR) { cs = 0; cmin = PR; }
-        }
+        for (int b = 0; b < D; b++) slot(b);
     }
+#pragma unroll
+    for (int b = 0; b < D - 1; b++)
+        if (ks + b < nstream) slot(b);
 
     // ---- per tap: sum the four waves' tiles, then write
     constexpr int RI = 32 * NI, RJ = 32 * NJ;
